@@ -113,6 +113,8 @@ struct xc_handle {
   void* wo_c = nullptr; float* bo_c = nullptr; float* ln3_shift = nullptr; float* ln3_scale = nullptr;
   void* kc_c = nullptr; void* vt_c = nullptr; void* cond_act = nullptr; float* cond_kv = nullptr;
   float* ones = nullptr;
+  // per block, an upper bound of the (cross-)attention's |score| in log2 units
+  std::vector<float> score_bound, score_bound_c;
   // gate global channel from the MLP-down epilogue (bf16 models whose cameras
   // all have >= 32 tokens): partials, 32-row-block tables, per-pass input sums
   // and per-(t, b) residual sums
@@ -444,6 +446,29 @@ P* wptr(void* base, size_t elems_before, size_t esz) {
   return reinterpret_cast<P*>(reinterpret_cast<char*>(base) + elems_before * esz);
 }
 
+// The softmax scale 1 / sqrt(d) in log2 units; bf16 models fold it into the
+// stored queries.
+float softmax_scale(int D) { return 1.4426950408889634f / sqrtf((float)D); }
+
+// Upper bound of |q . k| / sqrt(d) in log2 units from the RMSNorm gains: a
+// normalised head vector has norm at most sqrt(d), so |q . k| <= d max_i
+// |gq_i gk_i|; a rotation mixes the dimensions of a pair, so the maximum then
+// is taken per pair.  2% cover the rounding of q and k to bf16 (2^-8 each).
+float qk_score_bound(const float* gq, const float* gk, int D, bool rope) {
+  const int step = rope ? 2 : 1;
+  float most = 0.f;
+  for (int i = 0; i + step <= D; i += step) {
+    float a = 0.f, b = 0.f;
+    for (int j = i; j < i + step; ++j) {
+      if (!std::isfinite(gq[j]) || !std::isfinite(gk[j])) return INFINITY;
+      a = std::max(a, std::fabs(gq[j]));
+      b = std::max(b, std::fabs(gk[j]));
+    }
+    most = std::max(most, a * b);
+  }
+  return 1.02f * (float)D * softmax_scale(D) * most;
+}
+
 // Cross-attention layer of block b on x1 (in place): affine LayerNorm, q
 // projection with the per-head RMSNorm, attention over the condition's keys
 // and values, output projection added without a gate.
@@ -463,6 +488,7 @@ void cross_attention(xc_handle* h, int b, const int* flag, const PassWs& ws) {
     if (h->dtype == XC_BF16) {
       e.gq = h->gq_c + (size_t)b * D;
       e.gk = h->gk_c + (size_t)b * D;
+      e.q_scale = softmax_scale(D);
       e.q_out = h->q;
       e.H = H;
       e.D = D;
@@ -481,7 +507,7 @@ void cross_attention(xc_handle* h, int b, const int* flag, const PassWs& ws) {
     launch_attention(h->dtype, h->q, wptr<void>(h->kc_c, (size_t)b * H * h->Lcap_c * D, esz),
                      wptr<void>(h->vt_c, (size_t)b * H * h->Lcap_c * D, esz), h->o, ws.attn, ws.attn_floats, L,
                      (int)h->Mpad,
-                     (int)h->Lcap_c, h->n_cond, H, D, flag, h->st);
+                     (int)h->Lcap_c, h->n_cond, H, D, h->score_bound_c[b], flag, h->st);
   }
   {
     Prof p(h, XC_KERN_CROSS_O);
@@ -529,6 +555,7 @@ void compute_block(xc_handle* h, int b, const float* x, float* out, const int* f
     e.bias = h->bqkv + (size_t)b * 3 * C;
     e.gq = h->gq + (size_t)b * D;
     e.gk = h->gk + (size_t)b * D;
+    e.q_scale = softmax_scale(D);
     e.q_out = h->q;
     e.k_cache = kc_b;
     e.vt_cache = vt_b;
@@ -560,7 +587,7 @@ void compute_block(xc_handle* h, int b, const float* x, float* out, const int* f
   {
     Prof p(h, XC_KERN_ATTENTION);
     launch_attention(h->dtype, h->q, kc_b, vt_b, h->o, ws.attn, ws.attn_floats, L, (int)h->Mpad, (int)h->Lcap, (int)Lk,
-                     H, D, flag, h->st);
+                     H, D, h->score_bound[b], flag, h->st);
   }
   {
     Prof p(h, XC_KERN_GEMM_OPROJ);
@@ -840,6 +867,7 @@ void init_device(xc_handle* h, const float* w) {
     off += (size_t)C * Dm;
     upload(h, w + off, C, h->b2 + (size_t)b * C, false, stage);
     off += C;
+    h->score_bound.push_back(qk_score_bound(w + off, w + off + D, D, h->m.rope != 0));
     upload(h, w + off, D, h->gq + (size_t)b * D, false, stage);
     off += D;
     upload(h, w + off, D, h->gk + (size_t)b * D, false, stage);
@@ -862,6 +890,7 @@ void init_device(xc_handle* h, const float* w) {
       off += CC;
       upload(h, w + off, C, h->bo_c + (size_t)b * C, false, stage);
       off += C;
+      h->score_bound_c.push_back(qk_score_bound(w + off, w + off + D, D, false));
       upload(h, w + off, D, h->gq_c + (size_t)b * D, false, stage);
       off += D;
       upload(h, w + off, D, h->gk_c + (size_t)b * D, false, stage);

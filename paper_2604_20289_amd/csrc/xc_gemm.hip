@@ -324,7 +324,8 @@ __device__ __forceinline__ void qkv_epilogue(const EpiArgs& e, const f32x16 (&ac
     const int hd = (wn * NT * 32) / e.D;  // the wave's head within the tile
     float gv[NT];
 #pragma unroll
-    for (int nt = 0; nt < NT; ++nt) gv[nt] = gain[wn * NT * 32 + nt * 32 + lo - hd * e.D];
+    for (int nt = 0; nt < NT; ++nt)
+      gv[nt] = gain[wn * NT * 32 + nt * 32 + lo - hd * e.D] * (part == 0 ? e.q_scale : 1.0f);
     // per (row, head) sum of squares over the head's D columns: the lane's
     // NT columns, then the half-wave's 32 lanes (value k = (mt*4 + g)*4 + r is
     // row wm*MT*32 + mt*32 + g*8 + hi*4 + r), then the D / 64 waves of the head

@@ -73,6 +73,7 @@ struct EpiArgs {
   int n_rb;
   const float* gq;     // [D]
   const float* gk;     // [D]
+  float q_scale;       // factor of q besides its gain (the softmax scale, in log2 units)
   void* q_out;         // [H][Mpad][D]
   void* k_cache;       // [H][Lcap][D], token m at row kv_off + m
   void* vt_cache;      // [H][D][Lcap], token m at column kv_off + m
@@ -169,10 +170,12 @@ void launch_rope_table(float2* tab, const RopeArgs& r, int n_slots, const int* s
 // across workgroups) for L queries over Lk keys, H heads of dimension D.
 size_t attention_workspace_floats(int L, int Lk, int H, int D);
 // ws: ws_floats floats of workspace; the key split is chosen among those
-// whose partials fit (none: no split).
+// whose partials fit (none: no split).  bf16: the queries are already scaled
+// by log2(e) / sqrt(D) (EpiArgs::q_scale); score_bound: an upper bound of
+// |q . k| in those units (infinity: none known).
 void launch_attention(int dtype, const void* q, const void* kring, const void* vtring, void* o, float* ws,
-                      size_t ws_floats, int L, int Mpad, int Lcap, int Lk, int H, int D, const int* flag,
-                      hipStream_t st);
+                      size_t ws_floats, int L, int Mpad, int Lcap, int Lk, int H, int D, float score_bound,
+                      const int* flag, hipStream_t st);
 void launch_axpby(float a, const float* x, float b, const float* y, float* out, long long n, hipStream_t st);
 void launch_pass_begin(const GateState& gs, int n_blocks, hipStream_t st);
 // Gated evaluation, first launch: fingerprint of x against the (t, b) cache

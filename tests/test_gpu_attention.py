@@ -1,0 +1,83 @@
+"""The two attention kernels (scores bounded by the RMSNorm gains, and the
+running-maximum one) against the CPU oracle where they can go wrong: one key
+tile, every phase of the three-slot tile ring, ragged last tiles and query
+blocks, both head dims, cross-attention's own gains.
+
+Tolerance: relative L2 2e-2 on y, y - x and the caches, the bf16 bar of the
+parity suite.  The projections are scaled so that attention carries most of
+y - x."""
+import math
+
+import numpy as np
+import pytest
+
+import synth
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+# tokens: with a window of 3 chunks the passes see 1 / 2 / 2, 2 / 4 / 5, 3 / 5 / 8
+# and 5 / 9 / 13 key tiles of 64
+TOKENS = {40: (1, 1, 2, 20), 100: (1, 2, 5, 10), 150: (1, 3, 5, 10), 257: (1, 1, 1, 257), 300: (2, 3, 5, 10)}
+# gains 1: |score| <= sqrt(128) log2(e) = 16.3; gains 2.5: 6.25 times that, past the bound of 64
+GAINS = {"bounded": 1.0, "running-max": 2.5}
+
+
+def _workload(tokens, head_dim, **kw):
+    return synth.Workload(
+        f"attention-h256-d{head_dim}-L{tokens}",
+        synth.ModelShape(1, 256, 256 // head_dim, head_dim, 256, 256, 16, synth.BF16, 1, 3,
+                         (synth.ViewGroup(*TOKENS[tokens]),), **kw),
+        synth.GateParams(), synth.StreamParams(3, 0.97, 0.02))
+
+
+def _weights(m, gain, cross_gain=1.0):
+    blob = synth.make_weights(m)
+    for b in range(m.n_blocks):
+        w = synth.split_block_weights(m, blob, b)
+        w["wv"] *= 4
+        w["wo"] *= 8
+        w["gq"][:] = gain
+        w["gk"][:] = -gain  # the bound takes magnitudes
+        if m.cond_len:
+            w["wv_c"] *= 4
+            w["wo_c"] *= 4
+            w["gq_c"][:] = cross_gain
+            w["gk_c"][:] = cross_gain
+    return blob
+
+
+def _run(w, blob, **kw):
+    from lockstep import Lockstep
+    ls = Lockstep(w, weights=blob, compute=np.float64)
+    try:
+        ls.run(w.stream.n_chunks, tol_rel_l2=2e-2, **kw)
+        print(f"[attention] {w.name}: worst {max(ls.worst.values()):.2e}", flush=True)
+    finally:
+        ls.close()
+
+
+@pytest.mark.parametrize("tokens", sorted(TOKENS))
+@pytest.mark.parametrize("head_dim", [64, 128])
+@pytest.mark.parametrize("kernel", sorted(GAINS))
+def test_attention_kernels(kernel, head_dim, tokens):
+    w = _workload(tokens, head_dim)
+    _run(w, _weights(w.model, GAINS[kernel]))
+
+
+@pytest.mark.parametrize("gain,cross_gain", [(1.0, 2.5), (2.5, 1.0)])
+def test_attention_kernels_rope_and_cross(gain, cross_gain):
+    """Each attention of a block takes the kernel that its own gains allow; 70 condition tokens leave a ragged tile."""
+    w = _workload(150, 128, rope=1, cond_len=70)
+    _run(w, _weights(w.model, gain, cross_gain))
+
+
+def test_uneven_gains_with_rotation():
+    """A rotation mixes the two dimensions of a pair: gains that alternate between 4 and 1/4 (products of 1 in every
+    dimension, pair bound 16) must not be taken as bounded by 1."""
+    w = _workload(150, 128, rope=1)
+    blob = _weights(w.model, 1.0)
+    t = synth.split_block_weights(w.model, blob, 0)
+    t["gq"][0::2], t["gq"][1::2] = 4.0, 0.25
+    t["gk"][0::2], t["gk"][1::2] = 0.25, 4.0
+    _run(w, blob)
