@@ -229,6 +229,16 @@ struct GemmTile {
   static constexpr int STAGE = (BM + BN) * GBK;                         // bf16 elements per stage
 };
 
+// One 16-byte chunk per lane, global -> LDS (lane l lands at byte 16 l of the
+// wave's 1 KB block), from byte off (per lane) past the wave-uniform base.  A
+// buffer load, not a global one: global LDS loads are FLAT instructions, and
+// while one is in flight the compiler turns every wait for an LDS read into
+// lgkmcnt(0).
+__device__ __forceinline__ void dma16(const bf16* base, int off, bf16* lds_block) {
+  const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16*>(base), (short)0, -1, 0x00020000);
+  __builtin_amdgcn_raw_ptr_buffer_load_lds(r, lds_block, 16, off, 0, 0, 0);
+}
+
 __device__ __forceinline__ int swz32(int row, int c) { return row * GBK + ((c ^ ((row >> 2) & 3)) << 3); }
 
 // LDS bytes of the QKV epilogue: q / k stage the tile row-major [BM][BN + 8]
@@ -567,12 +577,12 @@ __global__ __launch_bounds__(256, 2) void gemm_bf16_kernel(const bf16* __restric
 #pragma unroll
     for (int i = 0; i < A_INSTR; ++i) {
       const int I = wave + 4 * i, row = I * 16 + lrow, c = lpc ^ ((row >> 2) & 3);
-      __builtin_amdgcn_global_load_lds(Ab + (long long)row * K + kt * GBK + c * 8, sa + I * 512, 16, 0, 0);
+      dma16(Ab + kt * GBK, (row * K + c * 8) * 2, sa + I * 512);
     }
 #pragma unroll
     for (int i = 0; i < B_INSTR; ++i) {
       const int I = wave + 4 * i, row = I * 16 + lrow, c = lpc ^ ((row >> 2) & 3);
-      __builtin_amdgcn_global_load_lds(Wb + (long long)row * K + kt * GBK + c * 8, sb + I * 512, 16, 0, 0);
+      dma16(Wb + kt * GBK, (row * K + c * 8) * 2, sb + I * 512);
     }
   };
   auto compute = [&](int buf) __attribute__((always_inline)) {
@@ -657,12 +667,6 @@ constexpr int WBM = 256, WBK = 64;
 // distinct (row parity, chunk) pairs
 __device__ __forceinline__ int swz8(int r, int c) { return c ^ ((r & 7) ^ ((r >> 3) & 1)); }
 
-// one 16-byte chunk per lane, global -> LDS; lane l lands at byte 16 l of the
-// wave's 1 KB block
-__device__ __forceinline__ void dma16(const bf16* src, bf16* lds_block) {
-  __builtin_amdgcn_global_load_lds(src, lds_block, 16, 0, 0);
-}
-
 template <int MODE, int BN, int WMW>
 __global__ __launch_bounds__(512, 1) void gemm_bf16_wide(const bf16* __restrict__ A, const bf16* __restrict__ W,
                                                          int M, int N, int K, EpiArgs e,
@@ -702,7 +706,7 @@ __global__ __launch_bounds__(512, 1) void gemm_bf16_wide(const bf16* __restrict_
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
     const int row = (wave + 8 * i) * 8 + (lane >> 3);
-    goff[i] = row * K + swz8(row, lane & 7) * 8;
+    goff[i] = (row * K + swz8(row, lane & 7) * 8) * 2;
   }
   // fragment reads: row lo (plus multiples of 32), logical chunk 2 kk + hi;
   // the swizzle depends on the row's low 4 bits only
@@ -721,12 +725,12 @@ __global__ __launch_bounds__(512, 1) void gemm_bf16_wide(const bf16* __restrict_
   auto issue_a = [&](int kt, int slot) __attribute__((always_inline)) {
     bf16* sa = sbuf + slot * ASLOT;
 #pragma unroll
-    for (int i = 0; i < WBM / 64; ++i) dma16(Ab + goff[i] + kt * WBK, sa + (wave + 8 * i) * 512);
+    for (int i = 0; i < WBM / 64; ++i) dma16(Ab + kt * WBK, goff[i], sa + (wave + 8 * i) * 512);
   };
   auto issue_w = [&](int kt, int slot) __attribute__((always_inline)) {
     bf16* sb = sbuf + 2 * ASLOT + slot * WSLOT;
 #pragma unroll
-    for (int i = 0; i < BN / 64; ++i) dma16(Wb + goff[i] + kt * WBK, sb + (wave + 8 * i) * 512);
+    for (int i = 0; i < BN / 64; ++i) dma16(Wb + kt * WBK, goff[i], sb + (wave + 8 * i) * 512);
   };
   auto compute = [&](int aslot, int wslot) __attribute__((always_inline)) {
     const bf16* sa = sbuf + aslot * ASLOT + (wm * MT * 32) * WBK;
