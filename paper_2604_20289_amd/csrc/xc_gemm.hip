@@ -5,12 +5,11 @@
 // bf16 path, two kernels built on v_mfma_f32_32x32x16_bf16 with float
 // accumulation.  Both operands are K-contiguous (activations row-major,
 // weights [out][in]), so a lane's MFMA operand is one 16-byte LDS read, and
-// stage tiles go from global memory straight into LDS (global_load_lds).
-//  * gemm_bf16_wide: one 8-wave workgroup per CU, 256 x 256 tiles (QKV,
-//    MLP up) or 256 x 192 tiles (output and MLP-down projections), 64-deep
-//    stages;
+// stage tiles go from global memory straight into LDS (buffer loads).
+//  * gemm_bf16_wide: one 8-wave workgroup per CU, 256 x 256, 256 x 192 or
+//    192 x 256 tiles, 64-deep stages;
 //  * gemm_bf16_kernel: (64*MT) x 128 tiles, two workgroups per CU, 32-deep
-//    stages; widths the wide tiles do not divide.
+//    stages; widths the wide tiles do not divide, small products.
 // Both run the element-wise epilogues through tile_epilogue (software-
 // pipelined operand loads, range-checked buffer stores) and the QKV epilogue
 // through qkv_epilogue.
@@ -237,6 +236,13 @@ struct GemmTile {
 __device__ __forceinline__ void dma16(const bf16* base, int off, bf16* lds_block) {
   const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16*>(base), (short)0, -1, 0x00020000);
   __builtin_amdgcn_raw_ptr_buffer_load_lds(r, lds_block, 16, off, 0, 0, 0);
+}
+
+// workgroup barrier that waits for nothing by itself
+__device__ __forceinline__ void lds_barrier() {
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
 }
 
 __device__ __forceinline__ int swz32(int row, int c) { return row * GBK + ((c ^ ((row >> 2) & 3)) << 3); }
@@ -565,7 +571,7 @@ __global__ __launch_bounds__(256, 2) void gemm_bf16_kernel(const bf16* __restric
       for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
 
   const int KT = K / GBK;
-  // Stages go global -> LDS directly (global_load_lds_dwordx4): one wave
+  // Stages go global -> LDS directly: one wave
   // instruction fills 1 KB of LDS lane-linearly, i.e. 16 rows x 4 chunks; a
   // lane fetches the logical chunk that the swizzle places at its position.
   constexpr int A_INSTR = T::BM / 16 / 4, B_INSTR = T::BN / 16 / 4;  // per wave
@@ -642,46 +648,58 @@ __global__ __launch_bounds__(256, 2) void gemm_bf16_kernel(const bf16* __restric
 }
 
 // ---------------------------------------------------------------------------
-// Wide bf16 MFMA GEMM: one workgroup of 8 waves per CU owns a 256 x BN tile,
+// Wide bf16 MFMA GEMM: one workgroup of 8 waves per CU owns a BM x BN tile,
 // its waves in a WMW x (8 / WMW) arrangement: 256 x 256 tiles as 2 x 4 waves
-// of 128 x 64 (4 x 2 accumulators each, as in gemm_bf16_kernel), 256 x 192
-// tiles as 4 x 2 waves of 64 x 96 (2 x 3).  Stages are 64 deep: every DMA
-// request fetches 128 contiguous bytes of a row (a whole cache line; the
-// request stream measures 14.6 TB/s with the 64-byte segments of 32-deep
-// stages against 24.5 TB/s with 128-byte ones, xc_lds_dma_rate), and per
-// output element a 256 x 256 tile moves a third fewer operand bytes than two
-// 256 x 128 tiles.  The weights have a ring of three stage slots and the
-// activations one of two (160 KB for 256 x 256 tiles, 136 KB for 256 x 192):
-// weights are requested two steps ahead, activations one step ahead, both at
-// the top of a step while the current stage is multiplied.  LDS rows are 128
-// bytes with their 16-byte chunks XOR-swizzled (swz8) so the 32 rows a
-// half-wave reads at one chunk position fall in distinct banks.  256 x 256
-// tiles serve the QKV and MLP-up projections (N % 256 == 0, K % 64 == 0, and
-// C % 256 == 0 for QKV), 256 x 192 tiles the output and MLP-down projections
-// (N % 192 == 0).
+// of 128 x 64 (4 x 2 accumulators each), 256 x 192 as 4 x 2 waves of 64 x 96
+// (2 x 3), 192 x 256 as 2 x 4 waves of 96 x 64 (3 x 2).  Stages are 64 deep:
+// every DMA request fetches 128 contiguous bytes of a row (a whole cache
+// line; the request stream measures 14.6 TB/s with the 64-byte segments of
+// 32-deep stages against 24.5 TB/s with 128-byte ones, xc_lds_dma_rate).
+// LDS rows are 128 bytes with their 16-byte chunks XOR-swizzled (swz8) so the
+// 32 rows a half-wave reads at one chunk position fall in distinct banks.
+//
+// A step (one stage) is four 16-deep slices.  The fragments of a slice are
+// read between the MFMAs of the slice before it, across the step's barrier
+// too: the barrier sits before the last slice, when every fragment of the
+// stage is in registers and the next stage has landed, and waits for nothing
+// else.  One operand has three ring slots and is requested two steps ahead,
+// the other two slots, requested right after the barrier that releases one.
+// The requests are spread over the MFMAs: a wave that issues its 7 or 8 in a
+// row waits for the address path (a stage's 56 - 64 KB take about as long as
+// its MFMAs) and its MFMAs wait behind them; with the operands held in the
+// caches the MLP-down loop then ran 137 us, spread 80 us of 2.2 GHz MFMAs.
+// Which operand gets three slots was measured: the activations for 256 x 256
+// tiles, the weights for the others (MLP down 132.5 against 144.5 us).
+// What remains is the L2-miss traffic (a third of the MLP-down requests).
+//
+// Measured in the full pass, interleaved runs, against fragments read at the
+// top of each slice and requests at the top of each step: multi-camera QKV
+// 105.6 -> 97 us, MLP up 138 -> 123, output projection 50.7 -> 46, MLP down
+// 147 -> 133; hidden 2048, 12096 tokens: QKV 308 -> 266, MLP up 370 -> 329.
 // ---------------------------------------------------------------------------
-constexpr int WBM = 256, WBK = 64;
+constexpr int WBK = 64;
 
 // physical 16-byte chunk of logical chunk c in a 128-byte LDS row r (an
 // involution in c): any 8 consecutive rows at distinct chunks, any 16 at
 // distinct (row parity, chunk) pairs
 __device__ __forceinline__ int swz8(int r, int c) { return c ^ ((r & 7) ^ ((r >> 3) & 1)); }
 
-template <int MODE, int BN, int WMW>
+template <int MODE, int BM, int BN, int WMW, bool AAHEAD>
 __global__ __launch_bounds__(512, 1) void gemm_bf16_wide(const bf16* __restrict__ A, const bf16* __restrict__ W,
                                                          int M, int N, int K, EpiArgs e,
                                                          const int* __restrict__ flag) {
   if (flag != nullptr && *flag) return;
-  constexpr int WNW = 8 / WMW, MT = WBM / 32 / WMW, NT = BN / 32 / WNW;
-  static_assert(MT * 32 * WMW == WBM && NT * 32 * WNW == BN && BN % 64 == 0, "wide tile shape");
-  constexpr int ASLOT = WBM * WBK, WSLOT = BN * WBK;  // bf16 elements of one A / W stage slot
-  constexpr int MAIN_BYTES = (2 * ASLOT + 3 * WSLOT) * 2;  // A ring of 2, W ring of 3
-  constexpr int EPI_BYTES = MODE == EPI_QKV ? qkv_epi_bytes<WBM, BN, NT>() : 0;
+  constexpr int WNW = 8 / WMW, MT = BM / 32 / WMW, NT = BN / 32 / WNW;
+  static_assert(MT * 32 * WMW == BM && NT * 32 * WNW == BN && BM % 64 == 0 && BN % 64 == 0, "wide tile shape");
+  constexpr int ASLOT = BM * WBK, WSLOT = BN * WBK;  // bf16 elements of one A / W stage slot
+  constexpr int AR = AAHEAD ? 3 : 2, WR = 5 - AR;        // ring slots of A and W
+  constexpr int MAIN_BYTES = (AR * ASLOT + WR * WSLOT) * 2;
+  constexpr int EPI_BYTES = MODE == EPI_QKV ? qkv_epi_bytes<BM, BN, NT>() : 0;
   constexpr int LDS_BYTES = MAIN_BYTES > EPI_BYTES ? MAIN_BYTES : EPI_BYTES;
   __shared__ __attribute__((aligned(1024))) char lds[LDS_BYTES];
   bf16* sbuf = reinterpret_cast<bf16*>(lds);
 
-  const int n_tm = (M + WBM - 1) / WBM, n_tn = N / BN;
+  const int n_tm = (M + BM - 1) / BM, n_tn = N / BN;
   const int total = n_tm * n_tn;
   const int per_xcd = (total + kXcd - 1) / kXcd;
   const int t = (blockIdx.x % kXcd) * per_xcd + blockIdx.x / kXcd;
@@ -691,7 +709,7 @@ __global__ __launch_bounds__(512, 1) void gemm_bf16_wide(const bf16* __restrict_
   const int first_m = (t / in_group) * GM;
   const int gm = min(GM, n_tm - first_m);
   const int tm = first_m + (t % in_group) % gm, tn = (t % in_group) / gm;
-  const int m0 = tm * WBM, n0 = tn * BN;
+  const int m0 = tm * BM, n0 = tn * BN;
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -722,76 +740,93 @@ __global__ __launch_bounds__(512, 1) void gemm_bf16_wide(const bf16* __restrict_
       for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
 
   const int KT = K / WBK;
-  auto issue_a = [&](int kt, int slot) __attribute__((always_inline)) {
-    bf16* sa = sbuf + slot * ASLOT;
-#pragma unroll
-    for (int i = 0; i < WBM / 64; ++i) dma16(Ab + kt * WBK, goff[i], sa + (wave + 8 * i) * 512);
+  // request i of stage kt of an operand into a ring slot (past the last
+  // stage: the last one again, into a slot nobody reads any more)
+  auto dma_a = [&](int kt, int slot, int i) __attribute__((always_inline)) {
+    dma16(Ab + min(kt, KT - 1) * WBK, goff[i], sbuf + slot * ASLOT + (wave + 8 * i) * 512);
   };
-  auto issue_w = [&](int kt, int slot) __attribute__((always_inline)) {
-    bf16* sb = sbuf + 2 * ASLOT + slot * WSLOT;
-#pragma unroll
-    for (int i = 0; i < BN / 64; ++i) dma16(Wb + kt * WBK, goff[i], sb + (wave + 8 * i) * 512);
+  auto dma_w = [&](int kt, int slot, int i) __attribute__((always_inline)) {
+    dma16(Wb + min(kt, KT - 1) * WBK, goff[i], sbuf + AR * ASLOT + slot * WSLOT + (wave + 8 * i) * 512);
   };
-  auto compute = [&](int aslot, int wslot) __attribute__((always_inline)) {
+  bf16x8 fa[2][MT], fb[2][NT];
+  auto read = [&](int aslot, int wslot, int kk, int set, int i) __attribute__((always_inline)) {
     const bf16* sa = sbuf + aslot * ASLOT + (wm * MT * 32) * WBK;
-    const bf16* sb = sbuf + 2 * ASLOT + wslot * WSLOT + (wn * NT * 32) * WBK;
+    const bf16* sb = sbuf + AR * ASLOT + wslot * WSLOT + (wn * NT * 32) * WBK;
+    if (i < NT) fb[set][i] = *reinterpret_cast<const bf16x8*>(sb + i * 32 * WBK + foff[kk]);
+    else fa[set][i - NT] = *reinterpret_cast<const bf16x8*>(sa + (i - NT) * 32 * WBK + foff[kk]);
+  };
+  // the MFMAs of one 16-deep slice; between them the fragment reads of the
+  // next slice and the slice's DMA requests
+  auto slice = [&](int set, int aslot, int wslot, int kk, auto&& request) __attribute__((always_inline)) {
 #pragma unroll
-    for (int kk = 0; kk < WBK / 16; ++kk) {
-      bf16x8 a[MT], b[NT];
-#pragma unroll
-      for (int mt = 0; mt < MT; ++mt) a[mt] = *reinterpret_cast<const bf16x8*>(sa + mt * 32 * WBK + foff[kk]);
-#pragma unroll
-      for (int nt = 0; nt < NT; ++nt) b[nt] = *reinterpret_cast<const bf16x8*>(sb + nt * 32 * WBK + foff[kk]);
-#pragma unroll
-      for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-        for (int nt = 0; nt < NT; ++nt)
-          acc[mt][nt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[mt], b[nt], acc[mt][nt], 0, 0, 0);
+    for (int j = 0; j < MT * NT; ++j) {
+      if (j < MT + NT) read(aslot, wslot, kk, set ^ 1, j);
+      request(j);
+      acc[j / NT][j % NT] =
+          __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[set][j / NT], fb[set][j % NT], acc[j / NT][j % NT], 0, 0, 0);
+      __builtin_amdgcn_sched_barrier(0);
     }
   };
-  // A(k) lives in A slot k mod 2, W(k) in W slot k mod 3: the weights, which
-  // stream from HBM (the activations were just written and sit in the
-  // caches), are requested two steps ahead.  Step k requests A(k+1) and then
-  // W(k+2) (their slots were released by the barrier that ended step k-1),
-  // multiplies stage k, and waits for everything but the W(k+2) requests
-  // (vmcnt counts in issue order).  The barrier's workgroup release fence
-  // then also waits for those on this chip; a barrier without the fence,
-  // which leaves them in flight, measured the same (they land within a
-  // step), so the plain __syncthreads stays.
-#define XC_WAIT_VMCNT(n) __builtin_amdgcn_s_waitcnt((0x3f70) | ((n) & 15) | (((n) >> 4) << 14))
-  constexpr int WREQ = BN / 64;
-  issue_w(0, 0);
-  issue_a(0, 0);
-  if (KT > 1) {
-    issue_w(1, 1);
-    XC_WAIT_VMCNT(WREQ);
-  } else {
-    XC_WAIT_VMCNT(0);
+#define XC_WAIT(vm, lgkm) \
+  __builtin_amdgcn_s_waitcnt(0x70 | ((lgkm) << 8) | ((vm) & 15) | (((vm) >> 4) << 14))
+  constexpr int AREQ = BM / 64, WREQ = BN / 64, NREQ = AAHEAD ? WREQ : AREQ;  // NREQ: of the two-slot operand
+  static_assert(MT * NT >= MT + NT && MT * NT >= NREQ && AREQ <= 4 && WREQ <= 4, "requests and reads per slice");
+#pragma unroll
+  for (int k = 0; k < 2; ++k) {
+#pragma unroll
+    for (int i = 0; i < AREQ; ++i) dma_a(k, k, i);
+#pragma unroll
+    for (int i = 0; i < WREQ; ++i) dma_w(k, k, i);
   }
-  __syncthreads();
-  auto step = [&](int kt, int as, int ws) __attribute__((always_inline)) {
-    if (kt + 1 < KT) issue_a(kt + 1, as ^ 1);
-    if (kt + 2 < KT) issue_w(kt + 2, ws == 0 ? 2 : ws - 1);
-    compute(as, ws);
-    if (kt + 2 < KT) XC_WAIT_VMCNT(WREQ); else XC_WAIT_VMCNT(0);
-    __syncthreads();
+  XC_WAIT(AREQ + WREQ, 15);
+  lds_barrier();
+#pragma unroll
+  for (int i = 0; i < MT + NT; ++i) read(0, 0, 0, 0, i);
+  // s3, s2: kt mod 3 and mod 2 (the stage's slots in the two rings)
+  auto step = [&](int kt, int s3, int s2) __attribute__((always_inline)) {
+    const int s3n = s3 == 2 ? 0 : s3 + 1, s3p = s3 == 0 ? 2 : s3 - 1;
+    const int as = AAHEAD ? s3 : s2, ws = AAHEAD ? s2 : s3;
+    auto none = [](int) __attribute__((always_inline)) {};
+    // stage kt + 2 of the operand with three slots (its slot was released a
+    // step ago), spread over the first two slices
+    auto far = [&](int i) __attribute__((always_inline)) {
+      if constexpr (AAHEAD) { if (i < AREQ) dma_a(kt + 2, s3p, i); }
+      else { if (i < WREQ) dma_w(kt + 2, s3p, i); }
+    };
+    slice(0, as, ws, 1, [&](int j) __attribute__((always_inline)) { if (j % 3 == 1 && j < 6) far(j / 3); });
+    slice(1, as, ws, 2, [&](int j) __attribute__((always_inline)) { if (j % 3 == 1 && j < 6) far(2 + j / 3); });
+    slice(0, as, ws, 3, none);
+    // every fragment of stage kt is in registers; stage kt + 1 has landed
+    XC_WAIT(AAHEAD ? AREQ : WREQ, 0);
+    lds_barrier();
+    // stage kt + 2 of the other operand, into the slot just released
+    slice(1, AAHEAD ? s3n : s2 ^ 1, AAHEAD ? s2 ^ 1 : s3n, 0, [&](int j) __attribute__((always_inline)) {
+#pragma unroll
+      for (int i = 0; i < NREQ; ++i)
+        if (j == i * MT * NT / NREQ) {
+          if constexpr (AAHEAD) dma_w(kt + 2, s2, i);
+          else dma_a(kt + 2, s2, i);
+        }
+    });
   };
   int kt = 0;
-  for (; kt + 5 < KT; kt += 6) {
+  for (; kt + 6 < KT; kt += 6) {
     step(kt, 0, 0);
     step(kt + 1, 1, 1);
-    step(kt + 2, 0, 2);
-    step(kt + 3, 1, 0);
-    step(kt + 4, 0, 1);
-    step(kt + 5, 1, 2);
+    step(kt + 2, 2, 0);
+    step(kt + 3, 0, 1);
+    step(kt + 4, 1, 0);
+    step(kt + 5, 2, 1);
   }
-  for (; kt < KT; ++kt) step(kt, kt & 1, kt % 3);
-#undef XC_WAIT_VMCNT
+  for (; kt < KT; ++kt) step(kt, kt % 3, kt & 1);
+  XC_WAIT(0, 0);  // the epilogue may reuse the LDS: no request may still be landing
+#undef XC_WAIT
+  lds_barrier();
 
   if constexpr (MODE == EPI_QKV) {
-    qkv_epilogue<MT, NT, WBM, BN, 512>(e, acc, lds, m0, n0, M, wm, wn, tid, hi, lo);
+    qkv_epilogue<MT, NT, BM, BN, 512>(e, acc, lds, m0, n0, M, wm, wn, tid, hi, lo);
   } else {
-    tile_epilogue<MODE, MT, NT>(e, acc, m0, wm * MT * 32 + hi * 4, n0 + wn * NT * 32 + lo, M, WBM);
+    tile_epilogue<MODE, MT, NT>(e, acc, m0, wm * MT * 32 + hi * 4, n0 + wn * NT * 32 + lo, M, BM);
   }
 }
 
@@ -877,68 +912,77 @@ void launch_bf16(const void* A, const void* W, int M, int N, int K, const EpiArg
   gemm_bf16_kernel<MODE, MT, 2><<<grid, 256, 0, st>>>((const bf16*)A, (const bf16*)W, M, N, K, e, flag);
 }
 
-// Whether wide 256 x BN tiles beat the two-workgroup kernel for an M x N
-// product: a round's time taken in proportion to the tile area a CU works
-// through (two resident (64*MT) x 128 tiles share a CU), the wide kernel
-// 12% more efficient per flop (the multi-camera QKV product: 122.8 against
-// 137.5 us in one round-count class).  Small token counts leave most CUs
-// idle under wide tiles (768 tokens: 18 tiles of 256 x 256 for the QKV
-// product), where the smaller tiles win.
-bool wide_pays(int M, int N, int BN) {
-  const long long cus = cu_count();
-  const long long wt = (long long)((M + WBM - 1) / WBM) * (N / BN);
-  const double wide = (double)((wt + cus - 1) / cus) * WBM * BN / 1.12;
-  const int mt = pick_mt(M, N);
-  const long long t2 = (long long)((M + 64 * mt - 1) / (64 * mt)) * (N / 128);
-  const double two = (double)((t2 + 2 * cus - 1) / (2 * cus)) * (64.0 * mt * 128.0) * 2.0;
-  return wide <= two;
-}
-
-template <int MODE, int BN, int WMW>
+template <int MODE, int BM, int BN, int WMW, bool AAHEAD>
 void launch_wide(const void* A, const void* W, int M, int N, int K, const EpiArgs& e, const int* flag,
                  hipStream_t st) {
-  const int tiles = ((M + WBM - 1) / WBM) * (N / BN);
+  const int tiles = ((M + BM - 1) / BM) * (N / BN);
   const int grid = (tiles + kXcd - 1) / kXcd * kXcd;
-  gemm_bf16_wide<MODE, BN, WMW><<<grid, 512, 0, st>>>((const bf16*)A, (const bf16*)W, M, N, K, e, flag);
+  gemm_bf16_wide<MODE, BM, BN, WMW, AAHEAD><<<grid, 512, 0, st>>>((const bf16*)A, (const bf16*)W, M, N, K, e, flag);
+}
+
+long long rounds_of(int M, int N, int BM, int BN, int slots) {
+  const long long tiles = (long long)((M + BM - 1) / BM) * (N / BN);
+  return (tiles + slots - 1) / slots;
+}
+
+// Tile shape of an M x N product: 0: the two-workgroup kernel; 1: 256 x 256;
+// 2: 256 x 192; 3: 192 x 256 wide tiles.
+// Among the wide shapes a round costs in proportion to BM + BN: it is bound
+// by the operand bytes that a stage brings into LDS, not by its MFMAs (hidden
+// 2048, 12096 tokens: the QKV product takes 275 us in 5 rounds of 256 x 256
+// and 364 us in 6 of 192 x 256; the output and MLP-down products, 2 rounds
+// either way, 112 and 370 us in 192 x 256).  Against the two-workgroup kernel
+// (two resident (64*MT) x 128 tiles share a CU) a round costs in proportion
+// to the tile area, the wide kernel 25% more efficient (the same two products
+// there: 139 and 460 us, also in 2 rounds).  Small token counts leave most
+// CUs idle under wide tiles, where the smaller tiles win.
+int pick_wide(int M, int N, bool qkv) {
+  const int cus = cu_count();
+  static const struct { int shape, bm, bn; } kWide[] = {{1, 256, 256}, {2, 256, 192}, {3, 192, 256}};
+  int shape = 0;
+  long long best = 0;
+  double area = 0.0;
+  for (const auto& w : kWide) {
+    if (N % w.bn != 0 || (qkv && w.bn != 256)) continue;  // QKV: whole 64-column waves
+    const long long rounds = rounds_of(M, N, w.bm, w.bn, cus), c = rounds * (w.bm + w.bn);
+    if (shape == 0 || c < best) {
+      best = c;
+      shape = w.shape;
+      area = (double)rounds * w.bm * w.bn;
+    }
+  }
+  const int mt = pick_mt(M, N);
+  const double two = (double)rounds_of(M, N, 64 * mt, 128, 2 * cus) * (64.0 * mt * 128.0) * 2.0;
+  return shape != 0 && area / 1.25 <= two ? shape : 0;
 }
 
 template <int MODE>
 void launch_mode(int dtype, const void* A, const void* W, int M, int N, int K, const EpiArgs& e, const int* flag,
                  hipStream_t st) {
-  if (dtype == 1) {
-    // Wide tiles, measured at the multi-camera shapes: the QKV and MLP-up
-    // products on 256 x 256 (QKV 115 vs 140 us, MLP-up 156 vs 190 us against
-    // the two-workgroup kernel); the output and MLP-down projections on
-    // 256 x 192 (the same box in one call: 49.6 vs 51.3 us and 145.6 vs
-    // 147.6 us in the full pass against a persistent 4-wave kernel with
-    // 32-deep stages, which this replaced, and 49.8 vs 54.7 us and 146.1 vs
-    // 163.2 us against the two-workgroup kernel on 192 x 128 tiles; 256 x 256
-    // tiles leave 168 tiles for 256 CUs at hidden 1536).  Other widths: the
-    // two-workgroup kernel (at hidden 2048 it measured 445 vs 451 us for MLP
-    // down and 132 vs 136 us for the output projection against 256 x 256
-    // wide tiles), and products whose wide tiles leave the chip underfilled
-    // (wide_pays).
-    if constexpr (MODE == EPI_QKV || MODE == EPI_UP) {
-      if (N % 256 == 0 && K % WBK == 0 && (MODE != EPI_QKV || (e.H * e.D) % 256 == 0) && wide_pays(M, N, 256)) {
-        launch_wide<MODE, 256, 2>(A, W, M, N, K, e, flag, st);
-        return;
+  if constexpr (MODE != EPI_BIAS_F32) {
+    if (dtype == 1) {
+      constexpr bool qkv = MODE == EPI_QKV;
+      // a QKV tile lies in one of q, k, v
+      const bool wide_ok = K % WBK == 0 && (!qkv || (e.H * e.D) % 256 == 0);
+      switch (wide_ok ? pick_wide(M, N, qkv) : 0) {
+        case 1: launch_wide<MODE, 256, 256, 2, true>(A, W, M, N, K, e, flag, st); return;
+        case 2:
+          if constexpr (!qkv) launch_wide<MODE, 256, 192, 4, false>(A, W, M, N, K, e, flag, st);
+          return;
+        case 3: launch_wide<MODE, 192, 256, 2, false>(A, W, M, N, K, e, flag, st); return;
+        default: break;
       }
-    } else {
-      if (N % 192 == 0 && K % WBK == 0 && wide_pays(M, N, 192)) {
-        launch_wide<MODE, 192, 4>(A, W, M, N, K, e, flag, st);
-        return;
+      switch (pick_mt(M, N)) {
+        case 4: launch_bf16<MODE, 4>(A, W, M, N, K, e, flag, st); break;
+        case 3: launch_bf16<MODE, 3>(A, W, M, N, K, e, flag, st); break;
+        case 2: launch_bf16<MODE, 2>(A, W, M, N, K, e, flag, st); break;
+        default: launch_bf16<MODE, 1>(A, W, M, N, K, e, flag, st); break;
       }
+      return;
     }
-    switch (pick_mt(M, N)) {
-      case 4: launch_bf16<MODE, 4>(A, W, M, N, K, e, flag, st); break;
-      case 3: launch_bf16<MODE, 3>(A, W, M, N, K, e, flag, st); break;
-      case 2: launch_bf16<MODE, 2>(A, W, M, N, K, e, flag, st); break;
-      default: launch_bf16<MODE, 1>(A, W, M, N, K, e, flag, st); break;
-    }
-  } else {
-    dim3 grid((N + 63) / 64, (M + 63) / 64);
-    gemm_f32_kernel<MODE><<<grid, 256, 0, st>>>((const float*)A, (const float*)W, M, N, K, e, flag);
   }
+  dim3 grid((N + 63) / 64, (M + 63) / 64);
+  gemm_f32_kernel<MODE><<<grid, 256, 0, st>>>((const float*)A, (const float*)W, M, N, K, e, flag);
 }
 
 }  // namespace

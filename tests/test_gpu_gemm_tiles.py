@@ -1,0 +1,64 @@
+"""Tile shapes of the bf16 projections against the CPU oracle: the wide
+256 x 256, 256 x 192 and 192 x 256 tiles with ragged last row tiles, K of the
+fewest stages the ring handles (128: two) and of an odd number (384: six;
+1152: eighteen), in the QKV, output, MLP-up and MLP-down epilogues.
+
+Tolerance: relative L2 2e-2, the bf16 bar of the parity suite; the CPU side
+computes in float32 with bf16 storage rounding."""
+import numpy as np
+import pytest
+
+import synth
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+# On 256 CUs (rounds times BM + BN, then area against the two-workgroup kernel):
+#   h384-L16000: MLP up N = 384 on 256 x 192 (63 x 2 tiles), K = 384 and 384
+#   h1152-L7020: output and MLP-down products N = 1152 on 256 x 192, K = 1152
+#   h768-L16000: QKV, N = 2304, on wide tiles, K = 768
+#   h2048-L6100: output and MLP-down products, N = 2048, on 192 x 256 (32 x 8 tiles), K = 2048 and 128
+SHAPES = {
+    "h384-L16000": (384, 3, 384, (1, 1, 125, 128)),
+    "h1152-L7020": (1152, 9, 1152, (2, 3, 26, 45)),
+    "h768-L16000": (768, 6, 768, (1, 1, 125, 128)),
+    "h2048-L6100": (2048, 16, 128, (1, 1, 61, 100)),
+}
+
+
+@pytest.mark.parametrize("name", sorted(SHAPES))
+def test_wide_tiles(name):
+    """One block, one pass: the output on sampled rows (all keys and values count)."""
+    from lockstep import rel_l2
+    from oracle import xcache_oracle as xo
+    from paper_2604_20289_amd.xcache import XC_CACHE_KEYS, XC_CACHE_VALUES, XCache
+    C, H, Dm, grid = SHAPES[name]
+    m = synth.ModelShape(1, C, H, C // H, Dm, 256, 16, synth.BF16, 1, 1, (synth.ViewGroup(*grid),))
+    gate = synth.GateParams(front_anchors=0)
+    blob = synth.make_weights(m)
+    w = synth.split_block_weights(m, blob, 0)
+    w["b_ada"] += 0.5
+    L = m.tokens
+    x = next(iter(synth.latent_stream(m, synth.StreamParams(1, 0.9, 0.02), 0, 1)))
+    a = next(iter(synth.action_stream(m, synth.StreamParams(1, 0.9, 0.02), 0, 1)))
+    rows = np.unique(np.r_[np.arange(0, L, 997), [1, 31, 32, 191, 192, 255, 256, L - 193, L - 33, L - 2, L - 1]])
+    xc = XCache(m, gate, blob, torch.cuda.current_stream().cuda_stream)
+    try:
+        xd = torch.from_numpy(x).cuda()
+        yd = torch.empty_like(xd)
+        xc.forward_chunk(0, 1000.0, a, xd, yd)
+        k = torch.empty(L * C, dtype=torch.float32, device="cuda")
+        v = torch.empty_like(k)
+        xc.read_cache(XC_CACHE_KEYS, 0, 0, k)
+        xc.read_cache(XC_CACHE_VALUES, 0, 0, v)
+        got = yd.cpu().numpy()
+        k, v = (t.cpu().numpy().reshape(H, L, C // H) for t in (k, v))
+    finally:
+        xc.close()
+    orc = xo.XCacheOracle(m, gate, blob, np.float32)
+    c = orc.cond(1000.0, a)
+    want, (ko, vo) = orc.block(0, x.astype(np.float32), c, rows)
+    errs = {"y-x": rel_l2(got[rows] - x[rows], want - x[rows]), "K": rel_l2(k, ko), "V": rel_l2(v, vo)}
+    print(f"[gemm tiles] {name} L={L}: " + " ".join(f"{n} {e:.2e}" for n, e in errs.items()), flush=True)
+    for n, e in errs.items():
+        assert e <= 2e-2, (n, e)
