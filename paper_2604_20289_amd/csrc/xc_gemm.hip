@@ -6,10 +6,11 @@
 // accumulation.  Both operands are K-contiguous (activations row-major,
 // weights [out][in]), so a lane's MFMA operand is one 16-byte LDS read, and
 // stage tiles go from global memory straight into LDS (buffer loads).
-//  * gemm_bf16_wide: one 8-wave workgroup per CU, 256 x 256, 256 x 192 or
-//    192 x 256 tiles, 64-deep stages;
-//  * gemm_bf16_kernel: (64*MT) x 128 tiles, two workgroups per CU, 32-deep
-//    stages; widths the wide tiles do not divide, small products.
+//  * gemm_bf16_wide: one 8-wave workgroup per CU, 256 x 256 or 192 x 256
+//    tiles;
+//  * gemm_bf16_small: 4 waves, 64 x 64 to 192 x 128 tiles, one workgroup per
+//    CU with a deep stage ring or two with a shallow one.
+// pick_tile chooses.
 // Both run the element-wise epilogues through tile_epilogue (software-
 // pipelined operand loads, range-checked buffer stores) and the QKV epilogue
 // through qkv_epilogue.
@@ -206,27 +207,15 @@ __device__ __forceinline__ void tile_epilogue(const EpiArgs& e, const f32x16 (&a
 }
 
 // ---------------------------------------------------------------------------
-// bf16 MFMA GEMM.  Workgroup = 4 waves in a 2x2 arrangement; a wave owns an
-// (MT*32) x (NT*32) sub-tile, i.e. MT x NT independent 32x32 accumulators of
-// v_mfma_f32_32x32x16_bf16, so each 16-byte LDS fragment feeds several
-// MFMAs.  K advances 32 per stage; the A and B stage tiles (64-byte rows) go
-// from global memory straight into a 3-stage LDS ring (no staging
-// registers, no LDS store instructions), two stages ahead of the MFMAs, and
-// their 16-byte chunks are XOR-swizzled by (row / 4) so the rows a half-wave
-// reads fall in distinct banks.  The 1-D grid is dealt to the XCDs in
-// contiguous ranges of tiles, ordered in groups of 8 M-tiles x all N-tiles
-// so concurrently resident tiles share A row blocks and B column blocks in
-// the XCD's L2.
+// Operand staging shared by the two bf16 MFMA GEMMs.  The 1-D grid is dealt to
+// the XCDs in contiguous ranges of tiles, ordered in groups of 8 M-tiles x all
+// N-tiles so concurrently resident tiles share A row blocks and B column
+// blocks in the XCD's L2.  Stages are 64 deep: LDS rows of 128 bytes whose
+// 16-byte chunks are XOR-swizzled (swz8).
 // ---------------------------------------------------------------------------
 constexpr int kXcd = 8;
-constexpr int GBK = 32;
-
-template <int MT, int NT>
-struct GemmTile {
-  static constexpr int BM = 2 * MT * 32, BN = 2 * NT * 32;
-  static constexpr int A_PER_T = BM * 4 / 256, B_PER_T = BN * 4 / 256;  // 16-byte chunks per thread and stage
-  static constexpr int STAGE = (BM + BN) * GBK;                         // bf16 elements per stage
-};
+constexpr int WBK = 64;
+constexpr int WBN = 256;  // columns of the wide tiles
 
 // One 16-byte chunk per lane, global -> LDS (lane l lands at byte 16 l of the
 // wave's 1 KB block), from byte off (per lane) past the wave-uniform base.  A
@@ -245,7 +234,14 @@ __device__ __forceinline__ void lds_barrier() {
   asm volatile("" ::: "memory");
 }
 
-__device__ __forceinline__ int swz32(int row, int c) { return row * GBK + ((c ^ ((row >> 2) & 3)) << 3); }
+// physical 16-byte chunk of logical chunk c in a 128-byte LDS row r (an
+// involution in c): any 8 consecutive rows at distinct chunks, any 16 at
+// distinct (row parity, chunk) pairs
+__device__ __forceinline__ int swz8(int r, int c) { return c ^ ((r & 7) ^ ((r >> 3) & 1)); }
+
+// s_waitcnt vmcnt(vm) lgkmcnt(lgkm), expcnt left alone (gfx9 encoding)
+#define XC_WAIT(vm, lgkm) \
+  __builtin_amdgcn_s_waitcnt(0x70 | ((lgkm) << 8) | ((vm) & 15) | (((vm) >> 4) << 14))
 
 // LDS bytes of the QKV epilogue: q / k stage the tile row-major [BM][BN + 8]
 // bf16 followed by two [waves across N][BM] float arrays (partial sums of
@@ -533,19 +529,36 @@ __device__ __forceinline__ void qkv_epilogue(const EpiArgs& e, const f32x16 (&ac
   }
 }
 
-template <int MODE, int MT, int NT>
-__global__ __launch_bounds__(256, 2) void gemm_bf16_kernel(const bf16* __restrict__ A, const bf16* __restrict__ W,
-                                                           int M, int N, int K, EpiArgs e,
-                                                           const int* __restrict__ flag) {
+// ---------------------------------------------------------------------------
+// Small-tile bf16 MFMA GEMM: 4 waves in a 2 x 2 arrangement own a BM x BN tile,
+// BM = 64 MT, BN = 64 NT (a wave MT x NT accumulators).  It serves products
+// with few tiles, whose time is the chain of their stages: the ring of NS
+// stage slots keeps NS - 1 stages of requests in flight (128 x 128: five slots
+// with the CU to itself, two where two workgroups share it; a longer ring
+// than that costs more in its first stage's wait than it hides: 64 x 128 with
+// six slots 16.5 us, with three 15.5 at 768 x 512 x 2048).  Slices, barrier
+// and requests as in the wide kernel below; past the last stage nothing is
+// requested.  It replaced 32-deep stages (64-byte row segments) whose barrier
+// drained every request; interleaved runs, bit-identical:
+//   768 tokens, hidden 512: QKV 13.0 -> 10.1 us, output projection 10.7 ->
+//   8.4, MLP up 11.2 -> 8.4, MLP down 26.4 -> 14.1; 3510 tokens, hidden 768:
+//   QKV 31 -> 26, output 17.4 -> 14.5, MLP down 48.8 -> 31.0.
+// ---------------------------------------------------------------------------
+template <int MODE, int MT, int NT, int NS>
+__global__ __launch_bounds__(256, NS * (MT + NT) * 8 > 80 ? 1 : 2) void gemm_bf16_small(const bf16* __restrict__ A, const bf16* __restrict__ W,
+                                                          int M, int N, int K, EpiArgs e,
+                                                          const int* __restrict__ flag) {
   if (flag != nullptr && *flag) return;
-  typedef GemmTile<MT, NT> T;
-  constexpr int MAIN_BYTES = 3 * T::STAGE * 2;
-  constexpr int EPI_BYTES = MODE == EPI_QKV ? qkv_epi_bytes<T::BM, T::BN, NT>() : 0;
+  constexpr int BM = 64 * MT, BN = 64 * NT;
+  constexpr int STAGE = (BM + BN) * WBK;  // bf16 elements of one stage slot: A rows, then W rows
+  constexpr int MAIN_BYTES = NS * STAGE * 2;
+  constexpr int EPI_BYTES = MODE == EPI_QKV ? qkv_epi_bytes<BM, BN, NT>() : 0;
   constexpr int LDS_BYTES = MAIN_BYTES > EPI_BYTES ? MAIN_BYTES : EPI_BYTES;
-  __shared__ __attribute__((aligned(16))) char lds[LDS_BYTES];
+  static_assert(LDS_BYTES <= 160 * 1024, "ring fits");
+  __shared__ __attribute__((aligned(1024))) char lds[LDS_BYTES];
   bf16* sbuf = reinterpret_cast<bf16*>(lds);
 
-  const int n_tm = (M + T::BM - 1) / T::BM, n_tn = N / T::BN;
+  const int n_tm = (M + BM - 1) / BM, n_tn = N / BN;
   const int total = n_tm * n_tn;
   const int per_xcd = (total + kXcd - 1) / kXcd;
   const int t = (blockIdx.x % kXcd) * per_xcd + blockIdx.x / kXcd;
@@ -555,9 +568,10 @@ __global__ __launch_bounds__(256, 2) void gemm_bf16_kernel(const bf16* __restric
   const int first_m = (t / in_group) * GM;
   const int gm = min(GM, n_tm - first_m);
   const int tm = first_m + (t % in_group) % gm, tn = (t % in_group) / gm;
-  const int m0 = tm * T::BM, n0 = tn * T::BN;
+  const int m0 = tm * BM, n0 = tn * BN;
 
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave >> 1, wn = wave & 1;
   const int hi = lane >> 5, lo = lane & 31;
   const bf16* Ab = A + (long long)m0 * K;
@@ -570,89 +584,115 @@ __global__ __launch_bounds__(256, 2) void gemm_bf16_kernel(const bf16* __restric
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
 
-  const int KT = K / GBK;
-  // Stages go global -> LDS directly: one wave
-  // instruction fills 1 KB of LDS lane-linearly, i.e. 16 rows x 4 chunks; a
-  // lane fetches the logical chunk that the swizzle places at its position.
-  constexpr int A_INSTR = T::BM / 16 / 4, B_INSTR = T::BN / 16 / 4;  // per wave
-  constexpr int LOADS = A_INSTR + B_INSTR;
-  const int lrow = lane >> 2, lpc = lane & 3;
-  auto issue = [&](int kt, int buf) __attribute__((always_inline)) {
-    bf16* sa = sbuf + buf * T::STAGE;
-    bf16* sb = sa + T::BM * GBK;
+  const int KT = K / WBK;
+  // request i of a stage: rows 8I .. 8I+7, I = wave + 4i, of A (i < 2 MT) or
+  // W; lane l lands at row 8I + l/8, physical chunk l%8
+  constexpr int AREQ = 2 * MT, LOADS = 2 * MT + 2 * NT;
+  const int drow = wave * 8 + (lane >> 3);
+  int goff[MT > NT ? 2 * MT : 2 * NT];
 #pragma unroll
-    for (int i = 0; i < A_INSTR; ++i) {
-      const int I = wave + 4 * i, row = I * 16 + lrow, c = lpc ^ ((row >> 2) & 3);
-      dma16(Ab + kt * GBK, (row * K + c * 8) * 2, sa + I * 512);
-    }
-#pragma unroll
-    for (int i = 0; i < B_INSTR; ++i) {
-      const int I = wave + 4 * i, row = I * 16 + lrow, c = lpc ^ ((row >> 2) & 3);
-      dma16(Wb + kt * GBK, (row * K + c * 8) * 2, sb + I * 512);
-    }
-  };
-  auto compute = [&](int buf) __attribute__((always_inline)) {
-    const bf16* sa = sbuf + buf * T::STAGE;
-    const bf16* sb = sa + T::BM * GBK;
-#pragma unroll
-    for (int kk = 0; kk < GBK / 16; ++kk) {
-      const int c = kk * 2 + hi;
-      bf16x8 a[MT], b[NT];
-#pragma unroll
-      for (int mt = 0; mt < MT; ++mt) a[mt] = *reinterpret_cast<const bf16x8*>(&sa[swz32(wm * MT * 32 + mt * 32 + lo, c)]);
-#pragma unroll
-      for (int nt = 0; nt < NT; ++nt) b[nt] = *reinterpret_cast<const bf16x8*>(&sb[swz32(wn * NT * 32 + nt * 32 + lo, c)]);
-#pragma unroll
-      for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-        for (int nt = 0; nt < NT; ++nt)
-          acc[mt][nt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[mt], b[nt], acc[mt][nt], 0, 0, 0);
-    }
-  };
-  // vmcnt(n) with the other counters left at their maximum (gfx9 encoding)
-#define XC_WAIT_VMCNT(n) __builtin_amdgcn_s_waitcnt((0x3f70) | ((n) & 15) | (((n) >> 4) << 14))
-
-  // Stage k lives in LDS buffer k mod 3; stage k+2 is requested while stage k
-  // is multiplied, and stage k+1 (requested one step earlier) is waited for
-  // before the barrier.  Requests past the last stage repeat it (in bounds,
-  // into a buffer nobody reads again), so every step is the same code.
-  issue(0, 0);
-  issue(min(1, KT - 1), 1);
-  XC_WAIT_VMCNT(LOADS);
-  __syncthreads();
-  auto step = [&](int kt, int b0, int b2) __attribute__((always_inline)) {  // b0 = kt mod 3, b2 = (kt+2) mod 3
-    issue(min(kt + 2, KT - 1), b2);
-    compute(b0);
-    XC_WAIT_VMCNT(LOADS);
-    __syncthreads();
-  };
-  int kt = 0;
-  for (; kt + 2 < KT; kt += 3) {
-    step(kt, 0, 2);
-    step(kt + 1, 1, 0);
-    step(kt + 2, 2, 1);
+  for (int i = 0; i < (MT > NT ? 2 * MT : 2 * NT); ++i) {
+    const int row = drow + 32 * i;
+    goff[i] = (row * K + swz8(row, lane & 7) * 8) * 2;
   }
-  if (kt < KT) step(kt, 0, 2);
-  if (kt + 1 < KT) step(kt + 1, 1, 0);
-  XC_WAIT_VMCNT(0);  // the epilogue may reuse the LDS: no request may still be landing
-  __syncthreads();
-#undef XC_WAIT_VMCNT
+  auto request = [&](int kt, int slot, int i) __attribute__((always_inline)) {
+    bf16* dst = sbuf + slot * STAGE + (i < AREQ ? wave + 4 * i : BM / 8 + wave + 4 * (i - AREQ)) * 512;
+    if (i < AREQ) dma16(Ab + kt * WBK, goff[i], dst);
+    else dma16(Wb + kt * WBK, goff[i - AREQ], dst);
+  };
+  int foff[4];
+#pragma unroll
+  for (int kk = 0; kk < 4; ++kk) foff[kk] = lo * WBK + swz8(lo, 2 * kk + hi) * 8;
+#pragma unroll
+  for (int k = 0; k < NS; ++k)
+    if (k < KT) {
+#pragma unroll
+      for (int i = 0; i < LOADS; ++i) request(k, k, i);
+    }
+  if (KT >= NS) { XC_WAIT((NS - 1) * LOADS, 15); } else { XC_WAIT(0, 15); }
+  lds_barrier();
+  bf16x8 fa[2][MT], fb[2][NT];
+  auto read = [&](int slot, int kk, int set, int i) __attribute__((always_inline)) {
+    const bf16* sa = sbuf + slot * STAGE + (wm * MT * 32) * WBK;
+    const bf16* sb = sbuf + slot * STAGE + (BM + wn * NT * 32) * WBK;
+    if (i < NT) fb[set][i] = *reinterpret_cast<const bf16x8*>(sb + i * 32 * WBK + foff[kk]);
+    else fa[set][i - NT] = *reinterpret_cast<const bf16x8*>(sa + (i - NT) * 32 * WBK + foff[kk]);
+  };
+  // the MFMAs of one slice between the fragment reads of the next one and the
+  // slice's share of the requests (req: stage requested, or none)
+  auto slice = [&](int set, int slot, int kk, int req, int rslot, int r0, int r1) __attribute__((always_inline)) {
+    constexpr int STEPS = MT * NT > MT + NT ? MT * NT : MT + NT;
+#pragma unroll
+    for (int i = r0; i < r1; ++i)
+      if (req >= 0) request(req, rslot, i);
+#pragma unroll
+    for (int j = 0; j < STEPS; ++j) {
+      if (j < MT + NT) read(slot, kk, set ^ 1, j);
+      if (j < MT * NT)
+        acc[j / NT][j % NT] =
+            __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[set][j / NT], fb[set][j % NT], acc[j / NT][j % NT], 0, 0, 0);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+  };
+
+#pragma unroll
+  for (int i = 0; i < MT + NT; ++i) read(0, 0, 0, i);
+  // Step kt: slot s holds its stage, s1 the next one.  Before the last slice
+  // every fragment of the stage is in registers; stage kt + 1 has landed once
+  // at most `left` stages are still in flight; the slot goes to stage kt + NS,
+  // requested over the last slice and the next step's first three.
+  constexpr int Q = (LOADS + 3) / 4;
+  auto cut = [](int i) { return i * Q < LOADS ? i * Q : LOADS; };
+  int s = 0, prev = 0;
+  int kt = 0;
+  for (; kt + NS < KT; ++kt) {
+    const int s1 = s + 1 == NS ? 0 : s + 1;
+    // the rest of stage kt + NS - 1 goes to the previous step's slot
+    const int rest = kt > 0 ? kt + NS - 1 : -1;
+    slice(0, s, 1, rest, prev, cut(1), cut(2));
+    slice(1, s, 2, rest, prev, cut(2), cut(3));
+    slice(0, s, 3, rest, prev, cut(3), LOADS);
+    XC_WAIT((NS - 2) * LOADS, 0);
+    lds_barrier();
+    slice(1, s1, 0, kt + NS, s, 0, cut(1));
+    prev = s;
+    s = s1;
+  }
+  // the last NS steps (all of them when KT <= NS): nothing new is requested
+  const int rest = kt > 0 ? kt + NS - 1 : -1;
+  bool first = true;
+  for (; kt < KT; ++kt) {
+    const int s1 = s + 1 == NS ? 0 : s + 1;
+    slice(0, s, 1, first ? rest : -1, prev, cut(1), LOADS);
+    slice(1, s, 2, -1, 0, 0, 0);
+    slice(0, s, 3, -1, 0, 0, 0);
+    const int left = KT - 2 - kt;  // stages after the next one
+    if (left >= NS - 2 && NS > 2) { XC_WAIT((NS - 2) * LOADS, 0); }
+    else if (left >= 3 && NS > 5) { XC_WAIT(3 * LOADS, 0); }
+    else if (left == 2 && NS > 4) { XC_WAIT(2 * LOADS, 0); }
+    else if (left == 1 && NS > 3) { XC_WAIT(LOADS, 0); }
+    else { XC_WAIT(0, 0); }
+    lds_barrier();
+    slice(1, s1, 0, -1, 0, 0, 0);
+    first = false;
+    s = s1;
+  }
+  XC_WAIT(0, 0);  // the epilogue may reuse the LDS
+  lds_barrier();
 
   // accumulator element (mt, nt, g, r): tile row wm*MT*32 + mt*32 + g*8 + hi*4 + r,
   // tile column wn*NT*32 + nt*32 + lo
   if constexpr (MODE == EPI_QKV) {
-    qkv_epilogue<MT, NT, T::BM, T::BN, 256>(e, acc, lds, m0, n0, M, wm, wn, tid, hi, lo);
+    qkv_epilogue<MT, NT, BM, BN, 256>(e, acc, lds, m0, n0, M, wm, wn, tid, hi, lo);
   } else {
-    tile_epilogue<MODE, MT, NT>(e, acc, m0, wm * MT * 32 + hi * 4, n0 + wn * NT * 32 + lo, M, T::BM);
+    tile_epilogue<MODE, MT, NT>(e, acc, m0, wm * MT * 32 + hi * 4, n0 + wn * NT * 32 + lo, M, BM);
   }
 }
 
 // ---------------------------------------------------------------------------
-// Wide bf16 MFMA GEMM: one workgroup of 8 waves per CU owns a BM x BN tile,
-// its waves in a WMW x (8 / WMW) arrangement: 256 x 256 tiles as 2 x 4 waves
-// of 128 x 64 (4 x 2 accumulators each), 256 x 192 as 4 x 2 waves of 64 x 96
-// (2 x 3), 192 x 256 as 2 x 4 waves of 96 x 64 (3 x 2).  Stages are 64 deep:
-// every DMA request fetches 128 contiguous bytes of a row (a whole cache
+// Wide bf16 MFMA GEMM: one workgroup of 8 waves per CU owns a BM x 256 tile,
+// its waves in a 2 x 4 arrangement: 256 x 256 tiles of 128 x 64 (4 x 2
+// accumulators each), 192 x 256 of 96 x 64 (3 x 2).  Stages are 64 deep: every DMA request fetches 128 contiguous bytes of a row (a whole cache
 // line; the request stream measures 14.6 TB/s with the 64-byte segments of
 // 32-deep stages against 24.5 TB/s with 128-byte ones, xc_lds_dma_rate).
 // LDS rows are 128 bytes with their 16-byte chunks XOR-swizzled (swz8) so the
@@ -668,28 +708,22 @@ __global__ __launch_bounds__(256, 2) void gemm_bf16_kernel(const bf16* __restric
 // row waits for the address path (a stage's 56 - 64 KB take about as long as
 // its MFMAs) and its MFMAs wait behind them; with the operands held in the
 // caches the MLP-down loop then ran 137 us, spread 80 us of 2.2 GHz MFMAs.
-// Which operand gets three slots was measured: the activations for 256 x 256
-// tiles, the weights for the others (MLP down 132.5 against 144.5 us).
+// Which operand gets three slots (AAHEAD: the activations) was measured: the
+// activations for 256 x 256 tiles, the weights for 192 x 256 (hidden 2048,
+// 12096 tokens, MLP down 365 against 374 us).
 // What remains is the L2-miss traffic (a third of the MLP-down requests).
 //
 // Measured in the full pass, interleaved runs, against fragments read at the
 // top of each slice and requests at the top of each step: multi-camera QKV
-// 105.6 -> 97 us, MLP up 138 -> 123, output projection 50.7 -> 46, MLP down
+// 105.6 -> 97 us, MLP up 138 -> 123, output projection 50.7 -> 47, MLP down
 // 147 -> 133; hidden 2048, 12096 tokens: QKV 308 -> 266, MLP up 370 -> 329.
 // ---------------------------------------------------------------------------
-constexpr int WBK = 64;
-
-// physical 16-byte chunk of logical chunk c in a 128-byte LDS row r (an
-// involution in c): any 8 consecutive rows at distinct chunks, any 16 at
-// distinct (row parity, chunk) pairs
-__device__ __forceinline__ int swz8(int r, int c) { return c ^ ((r & 7) ^ ((r >> 3) & 1)); }
-
-template <int MODE, int BM, int BN, int WMW, bool AAHEAD>
+template <int MODE, int BM, bool AAHEAD>
 __global__ __launch_bounds__(512, 1) void gemm_bf16_wide(const bf16* __restrict__ A, const bf16* __restrict__ W,
                                                          int M, int N, int K, EpiArgs e,
                                                          const int* __restrict__ flag) {
   if (flag != nullptr && *flag) return;
-  constexpr int WNW = 8 / WMW, MT = BM / 32 / WMW, NT = BN / 32 / WNW;
+  constexpr int BN = WBN, WMW = 2, WNW = 8 / WMW, MT = BM / 32 / WMW, NT = BN / 32 / WNW;
   static_assert(MT * 32 * WMW == BM && NT * 32 * WNW == BN && BM % 64 == 0 && BN % 64 == 0, "wide tile shape");
   constexpr int ASLOT = BM * WBK, WSLOT = BN * WBK;  // bf16 elements of one A / W stage slot
   constexpr int AR = AAHEAD ? 3 : 2, WR = 5 - AR;        // ring slots of A and W
@@ -767,8 +801,6 @@ __global__ __launch_bounds__(512, 1) void gemm_bf16_wide(const bf16* __restrict_
       __builtin_amdgcn_sched_barrier(0);
     }
   };
-#define XC_WAIT(vm, lgkm) \
-  __builtin_amdgcn_s_waitcnt(0x70 | ((lgkm) << 8) | ((vm) & 15) | (((vm) >> 4) << 14))
   constexpr int AREQ = BM / 64, WREQ = BN / 64, NREQ = AAHEAD ? WREQ : AREQ;  // NREQ: of the two-slot operand
   static_assert(MT * NT >= MT + NT && MT * NT >= NREQ && AREQ <= 4 && WREQ <= 4, "requests and reads per slice");
 #pragma unroll
@@ -820,7 +852,6 @@ __global__ __launch_bounds__(512, 1) void gemm_bf16_wide(const bf16* __restrict_
   }
   for (; kt < KT; ++kt) step(kt, kt % 3, kt & 1);
   XC_WAIT(0, 0);  // the epilogue may reuse the LDS: no request may still be landing
-#undef XC_WAIT
   lds_barrier();
 
   if constexpr (MODE == EPI_QKV) {
@@ -883,77 +914,69 @@ int cu_count() {
   return cus;
 }
 
-// Rows per M-tile for an M x N product: the tile height (64*MT) whose tile
-// count best fills whole rounds of resident workgroups (2 per CU); 64-row
-// tiles only where even 128-row tiles leave CUs without one (small
-// products, e.g. 768 tokens), since they move more operand bytes per flop.
-int pick_mt(int M, int N) {
-  const int slots = 2 * cu_count();
-  int best = 4;
-  double best_cost = 1e300;
-  for (int mt = 4; mt >= 2; --mt) {
-    const long long tiles = (long long)((M + 64 * mt - 1) / (64 * mt)) * (N / 128);
-    const long long rounds = (tiles + slots - 1) / slots;
-    const double cost = (double)rounds * mt;  // one round costs in proportion to the tile height
-    if (cost < best_cost - 1e-9) {
-      best_cost = cost;
-      best = mt;
-    }
-  }
-  if (best == 2 && (long long)((M + 127) / 128) * (N / 128) < cu_count()) best = 1;
-  return best;
-}
-
-template <int MODE, int MT>
-void launch_bf16(const void* A, const void* W, int M, int N, int K, const EpiArgs& e, const int* flag, hipStream_t st) {
-  typedef GemmTile<MT, 2> T;
-  const int tiles = ((M + T::BM - 1) / T::BM) * (N / T::BN);
-  const int grid = (tiles + kXcd - 1) / kXcd * kXcd;
-  gemm_bf16_kernel<MODE, MT, 2><<<grid, 256, 0, st>>>((const bf16*)A, (const bf16*)W, M, N, K, e, flag);
-}
-
-template <int MODE, int BM, int BN, int WMW, bool AAHEAD>
-void launch_wide(const void* A, const void* W, int M, int N, int K, const EpiArgs& e, const int* flag,
-                 hipStream_t st) {
-  const int tiles = ((M + BM - 1) / BM) * (N / BN);
-  const int grid = (tiles + kXcd - 1) / kXcd * kXcd;
-  gemm_bf16_wide<MODE, BM, BN, WMW, AAHEAD><<<grid, 512, 0, st>>>((const bf16*)A, (const bf16*)W, M, N, K, e, flag);
-}
-
 long long rounds_of(int M, int N, int BM, int BN, int slots) {
   const long long tiles = (long long)((M + BM - 1) / BM) * (N / BN);
   return (tiles + slots - 1) / slots;
 }
 
-// Tile shape of an M x N product: 0: the two-workgroup kernel; 1: 256 x 256;
-// 2: 256 x 192; 3: 192 x 256 wide tiles.
-// Among the wide shapes a round costs in proportion to BM + BN: it is bound
-// by the operand bytes that a stage brings into LDS, not by its MFMAs (hidden
-// 2048, 12096 tokens: the QKV product takes 275 us in 5 rounds of 256 x 256
-// and 364 us in 6 of 192 x 256; the output and MLP-down products, 2 rounds
-// either way, 112 and 370 us in 192 x 256).  Against the two-workgroup kernel
-// (two resident (64*MT) x 128 tiles share a CU) a round costs in proportion
-// to the tile area, the wide kernel 25% more efficient (the same two products
-// there: 139 and 460 us, also in 2 rounds).  Small token counts leave most
-// CUs idle under wide tiles, where the smaller tiles win.
-int pick_wide(int M, int N, bool qkv) {
+// Tile of an M x N x K product.  Times are estimated in microseconds as rounds
+// * (fixed + K / 64 * stage), the constants fitted to launches of every tile at
+// 300 to 12096 rows, N and K 256 to 8192 (output and MLP products; fixed holds
+// the launch, the first stage's latency and the epilogue).  Small tiles run one
+// workgroup per CU with a deep ring or two with a shallow one; a shallow 64 x
+// 128 tile with its CU to itself takes its own line.
+//   768 x 512 x 2048 (MLP down): 64 x 64 14.1 us, 64 x 128 15.5, 128 x 128 21.6
+//   3245 x 1024 x 4096: 64 x 128 43.6, 128 x 128 deep 41.3, 192 x 128 58.9
+//   3510 x 2304 x 768 (QKV): 64 x 128 30.6, 128 x 128 shallow 26.1
+//   7020 x 1536 x 6144: 128 x 128 172, 192 x 128 142, 192 x 256 133, 256 x 256 161
+//   12096 x 6144 x 2048 (QKV): 256 x 256 275 (5 rounds), 192 x 256 364 (6 rounds)
+//   12096 x 2048 x 8192: 192 x 128 381, 192 x 256 365, 256 x 256 408
+struct Tile {
+  int id, bm, bn, per_cu;
+  double fixed, stage;
+};
+enum TileId { kT64x64, kT64x128, kT128x128deep, kT128x128, kT192x128deep, kT192x128, kT256x256, kT192x256 };
+constexpr Tile kTiles[] = {
+    {kT64x64, 64, 64, 1, 6.5, 0.24},         {kT64x128, 64, 128, 1, 6.0, 0.31},
+    {kT64x128, 64, 128, 2, 7.5, 0.60},       {kT128x128deep, 128, 128, 1, 8.5, 0.48},
+    {kT128x128, 128, 128, 2, 9.5, 0.93},     {kT192x128deep, 192, 128, 1, 10.0, 0.65},
+    {kT192x128, 192, 128, 2, 13.5, 1.38},    {kT256x256, 256, 256, 1, 12.0, 1.50},
+    {kT192x256, 192, 256, 1, 14.0, 1.31},
+};
+
+// C: columns of each of q, k, v for the QKV epilogue (0: another epilogue)
+int pick_tile(int M, int N, int K, int C) {
   const int cus = cu_count();
-  static const struct { int shape, bm, bn; } kWide[] = {{1, 256, 256}, {2, 256, 192}, {3, 192, 256}};
-  int shape = 0;
-  long long best = 0;
-  double area = 0.0;
-  for (const auto& w : kWide) {
-    if (N % w.bn != 0 || (qkv && w.bn != 256)) continue;  // QKV: whole 64-column waves
-    const long long rounds = rounds_of(M, N, w.bm, w.bn, cus), c = rounds * (w.bm + w.bn);
-    if (shape == 0 || c < best) {
-      best = c;
-      shape = w.shape;
-      area = (double)rounds * w.bm * w.bn;
+  int best = kT64x128;
+  double best_us = 1e300;
+  for (const Tile& t : kTiles) {
+    if (N % t.bn != 0) continue;
+    // a QKV tile lies in one of q, k, v, its waves hold 64 columns
+    if (C != 0 && (C % t.bn != 0 || t.id == kT64x64)) continue;
+    const long long tiles = (long long)((M + t.bm - 1) / t.bm) * (N / t.bn), slots = (long long)cus * t.per_cu;
+    const double us = (double)((tiles + slots - 1) / slots) * (t.fixed + K / 64 * t.stage);
+    if (us < best_us) {
+      best_us = us;
+      best = t.id;
     }
   }
-  const int mt = pick_mt(M, N);
-  const double two = (double)rounds_of(M, N, 64 * mt, 128, 2 * cus) * (64.0 * mt * 128.0) * 2.0;
-  return shape != 0 && area / 1.25 <= two ? shape : 0;
+  return best;
+}
+
+template <int MODE, int MT, int NT, int NS>
+void launch_small_tile(const void* A, const void* W, int M, int N, int K, const EpiArgs& e, const int* flag,
+                       hipStream_t st) {
+  const int tiles = ((M + 64 * MT - 1) / (64 * MT)) * (N / (64 * NT));
+  const int grid = (tiles + kXcd - 1) / kXcd * kXcd;
+  gemm_bf16_small<MODE, MT, NT, NS><<<grid, 256, 0, st>>>((const bf16*)A, (const bf16*)W, M, N, K, e, flag);
+}
+
+template <int MODE, int BM, bool AAHEAD>
+void launch_wide(const void* A, const void* W, int M, int N, int K, const EpiArgs& e, const int* flag,
+                 hipStream_t st) {
+  const int tiles = ((M + BM - 1) / BM) * (N / WBN);
+  const int grid = (tiles + kXcd - 1) / kXcd * kXcd;
+  gemm_bf16_wide<MODE, BM, AAHEAD><<<grid, 512, 0, st>>>((const bf16*)A, (const bf16*)W, M, N, K, e, flag);
 }
 
 template <int MODE>
@@ -962,21 +985,17 @@ void launch_mode(int dtype, const void* A, const void* W, int M, int N, int K, c
   if constexpr (MODE != EPI_BIAS_F32) {
     if (dtype == 1) {
       constexpr bool qkv = MODE == EPI_QKV;
-      // a QKV tile lies in one of q, k, v
-      const bool wide_ok = K % WBK == 0 && (!qkv || (e.H * e.D) % 256 == 0);
-      switch (wide_ok ? pick_wide(M, N, qkv) : 0) {
-        case 1: launch_wide<MODE, 256, 256, 2, true>(A, W, M, N, K, e, flag, st); return;
-        case 2:
-          if constexpr (!qkv) launch_wide<MODE, 256, 192, 4, false>(A, W, M, N, K, e, flag, st);
-          return;
-        case 3: launch_wide<MODE, 192, 256, 2, false>(A, W, M, N, K, e, flag, st); return;
-        default: break;
-      }
-      switch (pick_mt(M, N)) {
-        case 4: launch_bf16<MODE, 4>(A, W, M, N, K, e, flag, st); break;
-        case 3: launch_bf16<MODE, 3>(A, W, M, N, K, e, flag, st); break;
-        case 2: launch_bf16<MODE, 2>(A, W, M, N, K, e, flag, st); break;
-        default: launch_bf16<MODE, 1>(A, W, M, N, K, e, flag, st); break;
+      switch (pick_tile(M, N, K, qkv ? e.H * e.D : 0)) {
+        case kT64x64:
+          if constexpr (!qkv) launch_small_tile<MODE, 1, 1, 8>(A, W, M, N, K, e, flag, st);
+          break;
+        case kT64x128: launch_small_tile<MODE, 1, 2, 3>(A, W, M, N, K, e, flag, st); break;
+        case kT128x128deep: launch_small_tile<MODE, 2, 2, 5>(A, W, M, N, K, e, flag, st); break;
+        case kT128x128: launch_small_tile<MODE, 2, 2, 2>(A, W, M, N, K, e, flag, st); break;
+        case kT192x128deep: launch_small_tile<MODE, 3, 2, 4>(A, W, M, N, K, e, flag, st); break;
+        case kT192x128: launch_small_tile<MODE, 3, 2, 2>(A, W, M, N, K, e, flag, st); break;
+        case kT256x256: launch_wide<MODE, 256, true>(A, W, M, N, K, e, flag, st); break;
+        case kT192x256: launch_wide<MODE, 192, false>(A, W, M, N, K, e, flag, st); break;
       }
       return;
     }
@@ -987,7 +1006,7 @@ void launch_mode(int dtype, const void* A, const void* W, int M, int N, int K, c
 
 }  // namespace
 
-// bf16 requirements (checked by the caller): N % 128 == 0, K % 32 == 0, A has
+// bf16 requirements (checked by the caller): N % 128 == 0, K % 128 == 0, A has
 // at least roundup(M, 256) rows allocated; EPI_QKV needs C % 128 == 0 and
 // D in {64, 128}.
 void launch_gemm(int dtype, EpiMode mode, const void* A, const void* W, int M, int N, int K, const EpiArgs& e,
