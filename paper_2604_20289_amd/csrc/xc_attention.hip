@@ -747,9 +747,12 @@ __global__ __launch_bounds__(64 * kBWaves, 1) void attn_bounded_kernel(const bf1
 // Combines the S pieces of each item in a fixed order (deterministic):
 // O = sum_p w_p l_p Ohat_p / sum_p w_p l_p, w_p = 2^(m_p - M),
 // M = max_p m_p, Ohat_p the piece's normalised output.
-// One workgroup per 32 queries of an item; a thread owns one query and 16
-// consecutive head dims.
-template <int D>
+// A thread owns one query and 16 consecutive head dims.  It is a chain of
+// memory latencies, so loads are issued together: the statistics of all
+// pieces (SB >= S a compile-time bound; pieces past S repeat the last one) and
+// the outputs of up to 5 pieces at a time.  Attention of 768 tokens, 8 heads
+// of 64, 3072 keys in 10 pieces: 23.7 us with one piece after another, 19.3.
+template <int D, int SB>
 __global__ __launch_bounds__(256) void attn_merge_kernel(bf16* __restrict__ O, int L, int H, int n_qt, int n_split,
                                                          const float* __restrict__ ws,
                                                          const int* __restrict__ flag) {
@@ -765,22 +768,41 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(bf16* __restrict__ O, i
   if (q >= L) return;
   const long long stride = piece_floats(D);
   const float* base = ws + (long long)item * n_split * stride;
-  float M = -INFINITY;
-  for (int p = 0; p < n_split; ++p) M = fmaxf(M, base[p * stride + kQT * D / 2 + ql]);
-  float acc[16];
+  float m[SB], l[SB];
+#pragma unroll
+  for (int p = 0; p < SB; ++p) {
+    const float* pp = base + min(p, n_split - 1) * stride;
+    m[p] = pp[kQT * D / 2 + ql];
+    l[p] = pp[kQT * D / 2 + kQT + ql];
+  }
+  constexpr int CH = SB < 5 ? SB : 5;
+  float M = m[0], den = 0.f, acc[16];
+#pragma unroll
+  for (int p = 1; p < SB; ++p) M = fmaxf(M, m[p]);
 #pragma unroll
   for (int i = 0; i < 16; ++i) acc[i] = 0.f;
-  float den = 0.f;
-  for (int p = 0; p < n_split; ++p) {
-    const float* pp = base + p * stride;
-    const float w = __builtin_amdgcn_exp2f(pp[kQT * D / 2 + ql] - M) * pp[kQT * D / 2 + kQT + ql];
-    den += w;
-    const bf16x8* src = reinterpret_cast<const bf16x8*>(reinterpret_cast<const bf16*>(pp) + ql * D + d0);
-    const bf16x8 v0 = src[0], v1 = src[1];
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      acc[i] += w * (float)v0[i];
-      acc[8 + i] += w * (float)v1[i];
+  for (int c = 0; c < SB; c += CH) {
+    if (c >= n_split) break;
+    bf16x8 v[CH][2];
+#pragma unroll
+    for (int k = 0; k < CH; ++k) {
+      const float* pp = base + min(c + k, n_split - 1) * stride;
+      const bf16x8* src = reinterpret_cast<const bf16x8*>(reinterpret_cast<const bf16*>(pp) + ql * D + d0);
+      v[k][0] = src[0];
+      v[k][1] = src[1];
+    }
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int k = 0; k < CH; ++k) {
+      if (c + k >= SB) break;
+      const float w = c + k < n_split ? __builtin_amdgcn_exp2f(m[c + k] - M) * l[c + k] : 0.f;
+      den += w;
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        acc[i] += w * (float)v[k][0][i];
+        acc[8 + i] += w * (float)v[k][1][i];
+      }
     }
   }
   const float inv = 1.0f / den;
@@ -793,6 +815,16 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(bf16* __restrict__ O, i
   bf16* orow = O + (long long)q * H * D + h * D + d0;
   *reinterpret_cast<bf16x8*>(orow) = o0;
   *reinterpret_cast<bf16x8*>(orow + 8) = o1;
+}
+
+template <int D>
+void launch_merge(bf16* o, int L, int H, int n_qt, int n_split, const float* ws, const int* flag, hipStream_t st) {
+  const int grid = H * n_qt * (kQT / (256 / (D / 16)));
+  if (n_split <= 2) attn_merge_kernel<D, 2><<<grid, 256, 0, st>>>(o, L, H, n_qt, n_split, ws, flag);
+  else if (n_split == 3) attn_merge_kernel<D, 3><<<grid, 256, 0, st>>>(o, L, H, n_qt, n_split, ws, flag);
+  else if (n_split <= 5) attn_merge_kernel<D, 5><<<grid, 256, 0, st>>>(o, L, H, n_qt, n_split, ws, flag);
+  else if (n_split <= 10) attn_merge_kernel<D, 10><<<grid, 256, 0, st>>>(o, L, H, n_qt, n_split, ws, flag);
+  else attn_merge_kernel<D, 16><<<grid, 256, 0, st>>>(o, L, H, n_qt, n_split, ws, flag);
 }
 
 __global__ __launch_bounds__(64) void attn_f32_kernel(const float* __restrict__ Q, const float* __restrict__ Kc,
@@ -859,8 +891,9 @@ int resident_attention_groups() {
 // workgroup: rounds * (tiles per unit + 4 for the unit's prologue and
 // epilogue) + 4 S items / (resident workgroups) for the merge (fitted to
 // measured split sweeps on the multi-camera shapes, where it picks S = 3),
-// over S <= 16 with chunks of at least 4 tiles: few items over a long window
-// (768 tokens, 8 heads, 3072 keys: 24 items) take more splits; only split
+// over S <= 16 with chunks of at least 2 tiles: few items take more splits
+// (768 tokens, 8 heads, 3072 keys, 24 items: 10 splits 19.3 us, 5 splits 21.4,
+// none 47; 300 tokens, 2 heads, 600 keys: 5 splits 18.3 us, 2 splits 21.0); only split
 // counts whose partials fit in cap_floats workspace floats are considered
 // (S = 1 needs none).
 int attention_splits(int L, int Lk, int H, int D, size_t cap_floats) {
@@ -869,7 +902,7 @@ int attention_splits(int L, int Lk, int H, int D, size_t cap_floats) {
   const int slots = resident_attention_groups();
   int best = 1;
   double best_cost = 1e300;
-  for (int s = 1; s <= 16 && (s == 1 || NT / s >= 4); ++s) {
+  for (int s = 1; s <= 16 && (s == 1 || NT / s >= 2); ++s) {
     if (s > 1 && (size_t)items * s * (size_t)piece_floats(D) > cap_floats) break;
     const long long units = (long long)items * s;
     const long long rounds = (units + slots - 1) / slots;
@@ -910,7 +943,6 @@ void launch_attention(int dtype, const void* q, const void* kc, const void* vt, 
     const int n_split = attention_splits(L, Lk, H, D, ws != nullptr ? ws_floats : 0);
     const int units = H * n_split * n_qt;
     const int grid = (units + kXcds - 1) / kXcds * kXcds;
-    const int merge_grid = H * n_qt * (kQT / (256 / (D / 16)));
     const bool bounded = score_bound <= kMaxScoreBound;  // false for a NaN bound
 #define XC_ATTN(DD)                                                                                                \
   do {                                                                                                             \
@@ -921,7 +953,7 @@ void launch_attention(int dtype, const void* q, const void* kc, const void* vt, 
     else                                                                                                           \
       attn_bf16_kernel<DD><<<grid, 64 * kWaves, 0, st>>>((const bf16*)q, (const bf16*)kc, (const bf16*)vt,         \
                                                          (bf16*)o, L, Mpad, Lcap, Lk, H, n_qt, n_split, ws, flag); \
-    if (n_split > 1) attn_merge_kernel<DD><<<merge_grid, 256, 0, st>>>((bf16*)o, L, H, n_qt, n_split, ws, flag);   \
+    if (n_split > 1) launch_merge<DD>((bf16*)o, L, H, n_qt, n_split, ws, flag, st);                                \
   } while (0)
     if (D == 128)
       XC_ATTN(128);
