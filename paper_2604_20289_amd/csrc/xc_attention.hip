@@ -19,7 +19,7 @@
 //     accumulation is float.
 // Two kernels: attn_bounded_kernel where the RMSNorm gains bound the scores
 // (no running maximum), attn_bf16_kernel otherwise.
-// fp32 path: one wave per (query, head), plain online softmax.
+// fp32 path: one workgroup per (query, head), plain online softmax.
 #include "xc_internal.h"
 
 #include <math.h>
@@ -827,25 +827,42 @@ void launch_merge(bf16* o, int L, int H, int n_qt, int n_split, const float* ws,
   else attn_merge_kernel<D, 16><<<grid, 256, 0, st>>>(o, L, H, n_qt, n_split, ws, flag);
 }
 
-__global__ __launch_bounds__(64) void attn_f32_kernel(const float* __restrict__ Q, const float* __restrict__ Kc,
-                                                      const float* __restrict__ Vt, float* __restrict__ O, int L,
-                                                      int Mpad, int Lcap, int Lk, int H, int D, float scale,
-                                                      const int* __restrict__ flag) {
+// float32: one workgroup per (query, head), its 4 waves take 64-key chunks in
+// turn with an online softmax each and merge at the end.  Bound by latency, so
+// a lane's row of K (QK: one key per lane) and of V^T (PV: one head dim per
+// lane) are read as 16-byte loads in flight together where VEC (D % 4 == 0);
+// the scalar form takes any D <= 128.  64 queries, 128 keys, 4 heads of 32:
+// 17.8 us with one wave and scalar loads, 5.8 so.
+template <bool VEC>
+__global__ __launch_bounds__(256) void attn_f32_kernel(const float* __restrict__ Q, const float* __restrict__ Kc,
+                                                       const float* __restrict__ Vt, float* __restrict__ O, int L,
+                                                       int Mpad, int Lcap, int Lk, int H, int D, float scale,
+                                                       const int* __restrict__ flag) {
   if (flag != nullptr && *flag) return;
-  __shared__ float sq[128];
-  __shared__ float sp[64];
-  const int lane = threadIdx.x, q = blockIdx.x, h = blockIdx.y;
-  for (int i = lane; i < D; i += 64) sq[i] = Q[((long long)h * Mpad + q) * D + i];
+  __shared__ __attribute__((aligned(16))) float sq[128];
+  __shared__ __attribute__((aligned(16))) float sp[4][64];
+  __shared__ float sm[4], sl[4], so[4][128];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, q = blockIdx.x, h = blockIdx.y;
+  for (int i = threadIdx.x; i < D; i += 256) sq[i] = Q[((long long)h * Mpad + q) * D + i];
   __syncthreads();
   const float* Kh = Kc + (long long)h * Lcap * D;
   const float* Vh = Vt + (long long)h * D * Lcap;
   float m = -INFINITY, l = 0.f, o0 = 0.f, o1 = 0.f;
-  for (int k0 = 0; k0 < Lk; k0 += 64) {
+  for (int k0 = wave * 64; k0 < Lk; k0 += 256) {
     const int key = k0 + lane;
     float s = -INFINITY;
     if (key < Lk) {
       float acc = 0.f;
-      for (int i = 0; i < D; ++i) acc += sq[i] * Kh[(long long)key * D + i];
+      if constexpr (VEC) {
+        const float4* kr = reinterpret_cast<const float4*>(Kh + (long long)key * D);
+#pragma unroll 8
+        for (int i = 0; i < D / 4; ++i) {
+          const float4 kv = kr[i], qv = reinterpret_cast<const float4*>(sq)[i];
+          acc += qv.x * kv.x + qv.y * kv.y + qv.z * kv.z + qv.w * kv.w;
+        }
+      } else {
+        for (int i = 0; i < D; ++i) acc += sq[i] * Kh[(long long)key * D + i];
+      }
       s = acc * scale;
     }
     float mx = s;
@@ -858,19 +875,55 @@ __global__ __launch_bounds__(64) void attn_f32_kernel(const float* __restrict__ 
     l = l * alpha + ps;
     o0 *= alpha;
     o1 *= alpha;
-    sp[lane] = p;
-    __syncthreads();
+    sp[wave][lane] = p;
+    // the wave's own lanes read the probabilities: LDS operations of one wave
+    // complete in order, the fence keeps the compiler from reordering them
+    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+    __builtin_amdgcn_wave_barrier();
     const int nk = min(64, Lk - k0);
-    for (int jj = 0; jj < nk; ++jj) {
-      if (lane < D) o0 += sp[jj] * Vh[(long long)lane * Lcap + k0 + jj];
-      if (lane + 64 < D) o1 += sp[jj] * Vh[(long long)(lane + 64) * Lcap + k0 + jj];
-    }
-    __syncthreads();
+    auto pv = [&](int d, float o) __attribute__((always_inline)) {
+      const float* vr = Vh + (long long)d * Lcap + k0;
+      int jj = 0;
+      if constexpr (VEC) {
+#pragma unroll 4
+        for (; jj + 4 <= nk; jj += 4) {
+          const float4 vv = *reinterpret_cast<const float4*>(vr + jj);
+          const float4 pp = *reinterpret_cast<const float4*>(&sp[wave][jj]);
+          o += pp.x * vv.x + pp.y * vv.y + pp.z * vv.z + pp.w * vv.w;
+        }
+      }
+      for (; jj < nk; ++jj) o += sp[wave][jj] * vr[jj];
+      return o;
+    };
+    if (lane < D) o0 = pv(lane, o0);
+    if (lane + 64 < D) o1 = pv(lane + 64, o1);
+    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+    __builtin_amdgcn_wave_barrier();
     m = m_new;
   }
+  if (lane == 0) {
+    sm[wave] = m;
+    sl[wave] = l;
+  }
+  so[wave][lane] = o0;
+  so[wave][lane + 64] = o1;
+  __syncthreads();
+  // waves that saw no key have m = -inf and weight 0 (wave 0 always saw one)
+  const float M = fmaxf(fmaxf(sm[0], sm[1]), fmaxf(sm[2], sm[3]));
+  float w[4], den = 0.f;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    w[i] = i * 64 < Lk ? expf(sm[i] - M) : 0.f;
+    den += w[i] * sl[i];
+  }
   float* orow = O + (long long)q * H * D + h * D;
-  if (lane < D) orow[lane] = o0 / l;
-  if (lane + 64 < D) orow[lane + 64] = o1 / l;
+  for (int d = threadIdx.x; d < D; d += 256) {
+    float o = 0.f;
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      if (i * 64 < Lk) o += w[i] * so[i][d];
+    orow[d] = o / den;
+  }
 }
 
 }  // namespace
@@ -962,8 +1015,14 @@ void launch_attention(int dtype, const void* q, const void* kc, const void* vt, 
 #undef XC_ATTN
   } else {
     dim3 grid(L, H);
-    attn_f32_kernel<<<grid, 64, 0, st>>>((const float*)q, (const float*)kc, (const float*)vt, (float*)o, L, Mpad,
-                                         Lcap, Lk, H, D, 1.0f / sqrtf((float)D), flag);
+    const float scale = 1.0f / sqrtf((float)D);
+    // Lcap is a multiple of 64: with D % 4 == 0 every row of either cache is 16-byte aligned
+    if (D % 4 == 0)
+      attn_f32_kernel<true><<<grid, 256, 0, st>>>((const float*)q, (const float*)kc, (const float*)vt, (float*)o, L,
+                                                  Mpad, Lcap, Lk, H, D, scale, flag);
+    else
+      attn_f32_kernel<false><<<grid, 256, 0, st>>>((const float*)q, (const float*)kc, (const float*)vt, (float*)o, L,
+                                                   Mpad, Lcap, Lk, H, D, scale, flag);
   }
 }
 

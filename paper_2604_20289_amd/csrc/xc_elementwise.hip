@@ -264,12 +264,15 @@ __global__ __launch_bounds__(256) void ln_mod_kernel(const float* x, const float
   }
 }
 
-// QK RMSNorm and scatter.  Input: qkv [Mpad][3C] float (bias added).  One
-// workgroup per (64-token tile, head):
+// QK RMSNorm and scatter (float32 models).  Input: q, k, v columns of a
+// row-major float matrix (bias added).  One workgroup per (16 tokens, head):
 //   q  -> rms(q) * gq       -> Q  [H][Mpad][D]
 //   k  -> rms(k) * gk       -> K  cache [H][Lcap][D] at row kv_off + m
 //   v                       -> V^T cache [H][D][Lcap] at column kv_off + m
-// The V tile is transposed through LDS so the V^T rows are written coalesced.
+// Bound by latency: a wave takes 4 tokens and issues all their loads before
+// any arithmetic (64 tokens, 4 heads of 32, 16 tokens per wave one after
+// another: 28.6 us, so 6.2).  The V tile is transposed through LDS so the V^T rows are
+// written in runs of 16 tokens.
 template <typename T>
 __global__ __launch_bounds__(256) void qk_norm_kernel(const float* __restrict__ qs, const float* __restrict__ ks,
                                                       const float* __restrict__ vs, int ld,
@@ -278,23 +281,33 @@ __global__ __launch_bounds__(256) void qk_norm_kernel(const float* __restrict__ 
                                                       T* __restrict__ vtring, int L, int H, int D, int Mpad,
                                                       int Lcap, int kv_off, const int* __restrict__ flag) {
   if (flag != nullptr && *flag) return;
-  __shared__ float s_v[64][129];
+  constexpr int kTok = 16, kPerWave = kTok / 4;
+  __shared__ float s_v[kTok][129];
   const int tile = blockIdx.x, h = blockIdx.y;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int m0 = tile * 64;
-  // q and k: each wave takes 16 tokens; lane holds head dims lane, lane + 64
-  for (int i = 0; i < 16; ++i) {
-    int tl = wave * 16 + i;
-    int m = m0 + tl;
+  const int m0 = tile * kTok;
+  // lane holds head dims lane, lane + 64 of the wave's tokens
+  float a[2][kPerWave][2], v[kPerWave][2];
+#pragma unroll
+  for (int i = 0; i < kPerWave; ++i) {
+    const long long o = (long long)min(m0 + wave * kPerWave + i, L - 1) * ld + h * D;
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      const bool ok = lane + 64 * u < D;
+      a[0][i][u] = ok && qs != nullptr ? qs[o + lane + 64 * u] : 0.f;
+      a[1][i][u] = ok && ks != nullptr ? ks[o + lane + 64 * u] : 0.f;
+      v[i][u] = ok && vs != nullptr ? vs[o + lane + 64 * u] : 0.f;
+    }
+  }
+#pragma unroll
+  for (int i = 0; i < kPerWave; ++i) {
+    const int tl = wave * kPerWave + i, m = m0 + tl;
     if (m >= L) break;
 #pragma unroll
     for (int part = 0; part < 2; ++part) {
-      const float* base = part == 0 ? qs : ks;
-      if (base == nullptr) continue;
-      const float* src = base + (long long)m * ld + h * D;
+      if ((part == 0 ? qs : ks) == nullptr) continue;
       const float* g = part == 0 ? gq : gk;
-      float a0 = lane < D ? src[lane] : 0.f;
-      float a1 = lane + 64 < D ? src[lane + 64] : 0.f;
+      float a0 = a[part][i][0], a1 = a[part][i][1];
       float ss = wave_sum(a0 * a0 + a1 * a1);
       float r = 1.0f / sqrtf(ss / (float)D + 1e-6f);
       a0 = lane < D ? a0 * r * g[lane] : 0.f;
@@ -316,18 +329,15 @@ __global__ __launch_bounds__(256) void qk_norm_kernel(const float* __restrict__ 
       if (lane < D) dst[lane] = to_t<T>(a0);
       if (lane + 64 < D) dst[lane + 64] = to_t<T>(a1);
     }
-    if (vs != nullptr) {
-      const float* vsrc = vs + (long long)m * ld + h * D;
-      if (lane < D) s_v[tl][lane] = vsrc[lane];
-      if (lane + 64 < D) s_v[tl][lane + 64] = vsrc[lane + 64];
-    }
+    if (lane < D) s_v[tl][lane] = v[i][0];
+    if (lane + 64 < D) s_v[tl][lane + 64] = v[i][1];
   }
   if (vs == nullptr) return;
   __syncthreads();
-  // V^T: row dd holds 64 consecutive tokens
-  const int nt = min(64, L - m0);
-  for (int idx = threadIdx.x; idx < D * 64; idx += 256) {
-    int dd = idx >> 6, tl = idx & 63;
+  // V^T: row dd holds 16 consecutive tokens
+  const int nt = min(kTok, L - m0);
+  for (int idx = threadIdx.x; idx < D * kTok; idx += 256) {
+    const int dd = idx / kTok, tl = idx % kTok;
     if (tl < nt) vtring[((long long)h * D + dd) * Lcap + kv_off + m0 + tl] = to_t<T>(s_v[tl][dd]);
   }
 }
@@ -457,7 +467,7 @@ void launch_ln_mod(int dtype, const float* x, const float* shift, const float* s
 void launch_qk_norm(int dtype, const float* qs, const float* ks, const float* vs, int ld, const float* gq,
                     const float* gk, const RopeArgs& rope, void* q, void* kring, void* vtring, int L, int H, int D,
                     int Mpad, int Lcap, int kv_off, const int* flag, hipStream_t st) {
-  dim3 grid((L + 63) / 64, H);
+  dim3 grid((L + 15) / 16, H);
   if (dtype == 1)
     qk_norm_kernel<bf16><<<grid, 256, 0, st>>>(qs, ks, vs, ld, gq, gk, rope, (bf16*)q, (bf16*)kring,
                                                (bf16*)vtring, L, H, D, Mpad, Lcap, kv_off, flag);

@@ -15,8 +15,9 @@
 // pipelined operand loads, range-checked buffer stores) and the QKV epilogue
 // through qkv_epilogue.
 //
-// fp32 path: a plain LDS-tiled FMA GEMM (64x64 tiles, 4x4 per thread) used
-// for float32 models.
+// fp32 path (float32 models): gemm_f32_small on the float matrix instructions
+// for products with few tiles, a plain LDS-tiled FMA GEMM (64x64 tiles, 4x4 per
+// thread) beyond.
 #include "xc_internal.h"
 
 #include <math.h>
@@ -861,6 +862,74 @@ __global__ __launch_bounds__(512, 1) void gemm_bf16_wide(const bf16* __restrict_
   }
 }
 
+// float32 products with few output tiles (rows K-contiguous, K % 4 == 0).  The
+// 64 x 64 kernel below then runs on a handful of CUs, each waiting for two
+// barriers and a memory latency per 16 of K (64 x 128 x 512: 62 us on two
+// workgroups).  Here a workgroup owns a T16*16-square tile and its 4 waves
+// split K by 16-deep chunks: no staging, the operands go from memory to
+// v_mfma_f32_16x16x4_f32 (full float products, float accumulation) with four
+// chunks' loads in flight, and the waves' partial sums are added in a fixed
+// order through LDS (64 x 128 x 512: 5.4 us; QKV 64 x 384 x 128: 19.6 -> 3.4).
+// A lane holds 4 consecutive k of one row per chunk; MFMA
+// step j takes element j of both operands, i.e. k = 16 chunk + 4 (lane / 16) + j.
+template <int MODE, int T16>
+__global__ __launch_bounds__(256) void gemm_f32_small(const float* __restrict__ A, const float* __restrict__ W,
+                                                      int M, int N, int K, EpiArgs e, const int* __restrict__ flag) {
+  if (flag != nullptr && *flag) return;
+  constexpr int T = 16 * T16;
+  __shared__ float part[4][T][T + 1];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int m0 = blockIdx.y * T, n0 = blockIdx.x * T;
+  const int r = lane & 15, kq = (lane >> 4) * 4;
+  const float *a_row[T16], *w_row[T16];  // rows past the edge: the last one, never stored
+#pragma unroll
+  for (int i = 0; i < T16; ++i) {
+    a_row[i] = A + (long long)min(m0 + 16 * i + r, M - 1) * K;
+    w_row[i] = W + (long long)min(n0 + 16 * i + r, N - 1) * K;
+  }
+  f32x4 acc[T16][T16];
+#pragma unroll
+  for (int i = 0; i < T16; ++i)
+#pragma unroll
+    for (int j = 0; j < T16; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+  constexpr int U = 4;  // chunks in flight
+  const int chunks = (K + 15) / 16;
+  for (int c0 = wave; c0 < chunks; c0 += 4 * U) {
+    f32x4 a[U][T16], w[U][T16];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int k = (c0 + 4 * u) * 16 + kq;
+#pragma unroll
+      for (int i = 0; i < T16; ++i) {
+        a[u][i] = k < K ? *reinterpret_cast<const f32x4*>(a_row[i] + k) : f32x4{0.f, 0.f, 0.f, 0.f};
+        w[u][i] = k < K ? *reinterpret_cast<const f32x4*>(w_row[i] + k) : f32x4{0.f, 0.f, 0.f, 0.f};
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+#pragma unroll
+      for (int k = 0; k < 4; ++k)
+#pragma unroll
+        for (int i = 0; i < T16; ++i)
+#pragma unroll
+          for (int j = 0; j < T16; ++j)
+            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[u][i][k], w[u][j][k], acc[i][j], 0, 0, 0);
+  }
+#pragma unroll
+  for (int i = 0; i < T16; ++i)
+#pragma unroll
+    for (int j = 0; j < T16; ++j)
+#pragma unroll
+      for (int k = 0; k < 4; ++k) part[wave][16 * i + (lane >> 4) * 4 + k][16 * j + r] = acc[i][j][k];
+  __syncthreads();
+  for (int idx = threadIdx.x; idx < T * T; idx += 256) {
+    const int row = idx / T, col = idx % T;
+    if (m0 + row < M && n0 + col < N)
+      epilogue<MODE, float>(e, m0 + row, n0 + col,
+                            ((part[0][row][col] + part[1][row][col]) + part[2][row][col]) + part[3][row][col]);
+  }
+}
+
 template <int MODE>
 __global__ __launch_bounds__(256) void gemm_f32_kernel(const float* __restrict__ A, const float* __restrict__ W,
                                                        int M, int N, int K, EpiArgs e, const int* __restrict__ flag) {
@@ -999,6 +1068,20 @@ void launch_mode(int dtype, const void* A, const void* W, int M, int N, int K, c
       }
       return;
     }
+  }
+  // 16-byte rows; the operands are re-read by every tile, so the tiles grow
+  // with the product, up to the staged 64 x 64 ones
+  const long long t16 = (long long)((M + 15) / 16) * ((N + 15) / 16);
+  const bool rows16 = K % 4 == 0 && ((reinterpret_cast<unsigned long long>(A) | reinterpret_cast<unsigned long long>(W)) & 15) == 0;
+  if (rows16 && t16 <= 4ll * cu_count()) {
+    dim3 grid((N + 15) / 16, (M + 15) / 16);
+    gemm_f32_small<MODE, 1><<<grid, 256, 0, st>>>((const float*)A, (const float*)W, M, N, K, e, flag);
+    return;
+  }
+  if (rows16 && t16 <= 32ll * cu_count()) {
+    dim3 grid((N + 31) / 32, (M + 31) / 32);
+    gemm_f32_small<MODE, 2><<<grid, 256, 0, st>>>((const float*)A, (const float*)W, M, N, K, e, flag);
+    return;
   }
   dim3 grid((N + 63) / 64, (M + 63) / 64);
   gemm_f32_kernel<MODE><<<grid, 256, 0, st>>>((const float*)A, (const float*)W, M, N, K, e, flag);

@@ -1,0 +1,39 @@
+"""The float32 kernels where their dispatch changes, against the CPU oracle
+(max-abs 1e-4, the bar of the float32 model): products on 16- and 32-square
+tiles and on the staged 64 x 64 ones, K that is no multiple of 16 or of 4,
+ragged rows and columns; attention with 16-byte and scalar rows, fewer keys
+than a chunk, fewer chunks than waves and several per wave."""
+import pytest
+
+import synth
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+# name: (hidden, heads, mlp, kv_window, grid).  Tiles of 16 x 16 on 256 CUs: up to 1024 take
+# 16-square tiles, up to 8192 32-square ones (h256-L300: output 304, QKV 912, MLP 1216;
+# h512-L1100: output 2208, QKV 6624, MLP up 8832 on 64 x 64)
+MODELS = {
+    "h128-L64": (128, 4, 512, 2, (1, 4, 4, 4)),
+    "h256-L300": (256, 4, 1024, 2, (2, 3, 5, 10)),
+    "h512-L1100": (512, 8, 2048, 1, (1, 1, 25, 44)),
+    "h84-d28-mlp52": (84, 3, 52, 3, (1, 1, 7, 11)),       # K = 84 and 52: part of a 16-deep chunk
+    "h12-d6-mlp30": (12, 2, 30, 2, (1, 1, 3, 11)),        # rows of no multiple of 16 bytes (MLP down, heads)
+    "h128-d128-L20": (128, 1, 130, 4, (1, 1, 4, 5)),      # one head of 128, 20 to 80 keys
+}
+
+
+@pytest.mark.parametrize("rope", [0, 1])
+@pytest.mark.parametrize("name", sorted(MODELS))
+def test_f32_kernels(name, rope):
+    from lockstep import Lockstep
+    C, H, Dm, window, grid = MODELS[name]
+    m = synth.ModelShape(2, C, H, C // H, Dm, 64, 8, synth.F32, 1, window, (synth.ViewGroup(*grid),), rope=rope,
+                         cond_len=9 if rope else 0)
+    w = synth.Workload(f"f32-{name}", m, synth.GateParams(), synth.StreamParams(window + 1, 0.97, 0.02))
+    ls = Lockstep(w)
+    try:
+        ls.run(w.stream.n_chunks, tol_abs=1e-4)
+        print(f"[f32] {name} rope={rope}: worst {max(ls.worst.values()):.2e}", flush=True)
+    finally:
+        ls.close()
