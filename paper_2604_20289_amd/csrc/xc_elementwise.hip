@@ -135,17 +135,16 @@ __global__ __launch_bounds__(256) void adaln_kernel(const T* __restrict__ w, con
 
 // The same GEMV when a row of W_ada is a whole number of 16-byte chunks (every
 // supported conditioning width): the weights of all blocks form one
-// contiguous [rows][dc] matrix, and a wave takes 32 consecutive rows, i.e.
-// one contiguous span of 32 * cpr chunks, walked lane-linearly (every load
+// contiguous [rows][dc] matrix, and a wave takes kRows consecutive rows, i.e.
+// one contiguous span of kRows * cpr chunks, walked lane-linearly (every load
 // instruction reads 1 KB of consecutive bytes).  Each chunk's dot product with
 // its slice of SiLU(c) goes to LDS; lane r < 32 then sums row r's cpr
 // partials in order (deterministic).
-template <typename T>
+template <typename T, int kRows>
 __global__ __launch_bounds__(256) void adaln_flat_kernel(const T* __restrict__ w, const float* __restrict__ b,
                                                          const float* __restrict__ cond_silu, int n_rows, int dc,
                                                          float* __restrict__ mod) {
   constexpr int V = 16 / sizeof(T);
-  constexpr int kRows = 32;   // rows per wave
   constexpr int kBatch = 8;   // chunk loads in flight per lane
   typedef T tvec __attribute__((ext_vector_type(V)));
   __shared__ float s_c[kMaxCond];
@@ -224,15 +223,25 @@ __global__ __launch_bounds__(256) void ln_mod_kernel(const float* x, const float
     return;
   }
   float4 v[MAXV];
-  float s = 0.f;
+  // few columns: the modulation is loaded with the row, not a second memory
+  // latency later (wider rows keep the registers for more rows in flight)
+  constexpr bool kEarly = MAXV <= 2;
+  float4 msc[kEarly ? MAXV : 1], msh[kEarly ? MAXV : 1];
 #pragma unroll
   for (int i = 0; i < MAXV; ++i) {
-    int c4 = lane + i * 64;
+    const int c4 = lane + i * 64;
     if (c4 < C4) {
       v[i] = xr[c4];
-      s += (v[i].x + v[i].y) + (v[i].z + v[i].w);
+      if constexpr (kEarly) {
+        msc[i] = reinterpret_cast<const float4*>(scale)[c4];
+        msh[i] = reinterpret_cast<const float4*>(shift)[c4];
+      }
     }
   }
+  float s = 0.f;
+#pragma unroll
+  for (int i = 0; i < MAXV; ++i)
+    if (lane + i * 64 < C4) s += (v[i].x + v[i].y) + (v[i].z + v[i].w);
   const float mu = wave_sum(s) / (float)C;
   float q = 0.f;
 #pragma unroll
@@ -252,8 +261,8 @@ __global__ __launch_bounds__(256) void ln_mod_kernel(const float* x, const float
   for (int i = 0; i < MAXV; ++i) {
     int c4 = lane + i * 64;
     if (c4 < C4) {
-      float4 sc = reinterpret_cast<const float4*>(scale)[c4];
-      float4 sh = reinterpret_cast<const float4*>(shift)[c4];
+      const float4 sc = kEarly ? msc[kEarly ? i : 0] : reinterpret_cast<const float4*>(scale)[c4];
+      const float4 sh = kEarly ? msh[kEarly ? i : 0] : reinterpret_cast<const float4*>(shift)[c4];
       T4 o;
       o[0] = to_t<T>((v[i].x - mu) * rstd * (1.f + sc.x) + sh.x);
       o[1] = to_t<T>((v[i].y - mu) * rstd * (1.f + sc.y) + sh.y);
@@ -429,12 +438,23 @@ void launch_adaln(int dtype, const void* w_ada, const float* b_ada, const float*
   int total = rows_per_block * n_blocks;
   const int esz = dtype == 1 ? 2 : 4;
   if ((dc * esz) % 16 == 0 && block_stride_w == (long long)rows_per_block * dc) {
-    const int grid = (total + 127) / 128;  // 4 waves x 32 rows
-    const size_t lds = (size_t)4 * 32 * (dc * esz / 16) * sizeof(float);
-    if (dtype == 1)
-      adaln_flat_kernel<bf16><<<grid, 256, lds, st>>>((const bf16*)w_ada, b_ada, cond_silu, total, dc, mod);
-    else
-      adaln_flat_kernel<float><<<grid, 256, lds, st>>>((const float*)w_ada, b_ada, cond_silu, total, dc, mod);
+    // 32 rows per wave stream best once every CU has its workgroups; with fewer
+    // rows (models of few or narrow blocks) 8 spread them over the chip, one
+    // batch of loads per wave (HIP events: 8 blocks of hidden 512 10.2 -> 8.4 us, 2
+    // of 1536 12.7 -> 10.0)
+    const int rows = total >= 128 * 1024 ? 32 : 8;
+    const int grid = (total + 4 * rows - 1) / (4 * rows);
+    const size_t lds = (size_t)4 * rows * (dc * esz / 16) * sizeof(float);
+#define XC_ADALN(T, R) \
+  adaln_flat_kernel<T, R><<<grid, 256, lds, st>>>((const T*)w_ada, b_ada, cond_silu, total, dc, mod)
+    if (dtype == 1) {
+      if (rows == 32) XC_ADALN(bf16, 32);
+      else XC_ADALN(bf16, 8);
+    } else {
+      if (rows == 32) XC_ADALN(float, 32);
+      else XC_ADALN(float, 8);
+    }
+#undef XC_ADALN
     return;
   }
   int grid = (total + 31) / 32;  // 4 waves x 8 rows
