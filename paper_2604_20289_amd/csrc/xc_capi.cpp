@@ -968,11 +968,15 @@ GateArgs gate_args(xc_handle* h, int t, const float* action) {
   ga.strict0 = (t == 0 && h->g.step0_mode == XC_STEP0_STRICT) ? 1 : 0;
   ga.tau_strict0 = h->g.tau_strict0;
   ga.n_groups = h->m.n_groups;
-  ga.action_dim = h->have_action_prev ? h->A : 0;
+  ga.has_action = h->have_action_prev && h->A > 0;
+  double dot = 0, nn = 0, pp = 0;
   for (int i = 0; i < h->A; ++i) {
-    ga.action[i] = action[i];
-    ga.action_prev[i] = h->action_prev[i];
+    const double a = action[i], p = h->action_prev[i];
+    dot += a * p;
+    nn += a * a;
+    pp += p * p;
   }
+  ga.action_cos = dot / std::fmax(std::sqrt(nn) * std::sqrt(pp), 1e-12);
   for (int gi = 0; gi < kMaxGroups; ++gi) ga.spatial_count[gi] = h->spatial_count[gi];
   return ga;
 }

@@ -110,9 +110,8 @@ struct GateArgs {
   int strict0;          // 1 when this is step 0 in strict mode
   float tau_strict0;
   int n_groups;
-  int action_dim;       // 0: no action channel this pass
-  float action[kMaxAction];
-  float action_prev[kMaxAction];
+  int has_action;       // 0: no action channel this pass
+  double action_cos;    // Eq. 5 of the action channel (both vectors are known on the host)
   int spatial_count[kMaxGroups];  // entries in each group's spatial fingerprint
 };
 
