@@ -634,8 +634,10 @@ void compute_block(xc_handle* h, int b, const float* x, float* out, const int* f
   }
 }
 
-void pass_conditioning(xc_handle* h, float timestep, const float* action) {
-  launch_cond(action, h->Dt, h->A, timestep, h->cond, h->st);
+// A pass's conditioning vector and modulations; gated: a denoising pass, whose
+// skip flags and records start anew.
+void pass_conditioning(xc_handle* h, float timestep, const float* action, bool gated) {
+  launch_cond(action, h->Dt, h->A, timestep, h->cond, gate_state(h), gated ? h->B : 0, h->st);
   Prof p(h, XC_KERN_ADALN);
   launch_adaln(h->dtype, h->w_ada, h->b_ada, h->cond, 6 * h->C, (long long)6 * h->C * h->Dc, h->B, h->Dc, h->mod,
                h->st);
@@ -999,9 +1001,8 @@ xc_status forward_pass(xc_handle* h, int32_t step, float timestep, const float* 
     const xc_gate_config& g = h->g;
     const bool forced_all = !g.enabled || h->n < g.warmup || (flags & XC_FORCE_FULL) ||
                             (step == 0 && g.step0_mode == XC_STEP0_FORCE);
-    pass_conditioning(h, timestep, action_host);
-    GateState gs = gate_state(h);
-    launch_pass_begin(gs, h->B, h->st);
+    pass_conditioning(h, timestep, action_host, true);
+    const GateState gs = gate_state(h);
     const long long kv_off = (h->n % h->Wkv) * h->L;
     const long long Lk = std::min<long long>(h->n + 1, h->Wkv) * h->L;
     const GateArgs ga = gate_args(h, step, action_host);
@@ -1163,7 +1164,7 @@ xc_status xc_kv_update(xc_handle* h, float timestep, const float* action_host, c
   if (action_changed(h, action_host)) return XC_ERR_STATE;
   try {
     XC_HIP(hipSetDevice(h->device));
-    pass_conditioning(h, timestep, action_host);
+    pass_conditioning(h, timestep, action_host, false);
     const long long kv_off = (h->n % h->Wkv) * h->L;
     const long long Lk = std::min<long long>(h->n + 1, h->Wkv) * h->L;
     const float* x = reinterpret_cast<const float*>(x_clean);

@@ -51,7 +51,18 @@ struct CondArgs {
   float action[kMaxAction];
 };
 
-__global__ void cond_kernel(CondArgs a, int temb_dim, int action_dim, float timestep, float* cond_silu) {
+// A pass's first launch; n_blocks > 0 (a denoising pass) also resets the
+// per-block flags and records of the gate (a launch of its own cost the pass 4
+// us).
+__global__ void cond_kernel(CondArgs a, int temb_dim, int action_dim, float timestep, float* cond_silu, GateState gs,
+                            int n_blocks) {
+  for (int b = threadIdx.x; b < n_blocks; b += blockDim.x) {
+    gs.rec_dec[b] = 2;  // forced unless a decision kernel evaluates the block
+    gs.rec_s[b] = __builtin_nanf("");
+    gs.rec_d[b] = __builtin_nanf("");
+    gs.rec_tau[b] = __builtin_nanf("");
+    gs.flags[b] = 0;
+  }
   const int h = temb_dim / 2;
   for (int j = threadIdx.x; j < temb_dim + action_dim; j += blockDim.x) {
     double c;
@@ -405,16 +416,6 @@ __global__ void fill_f32_kernel(float* p, float v, long long n) {
   for (long long i = blockIdx.x * 256ll + threadIdx.x; i < n; i += (long long)gridDim.x * 256) p[i] = v;
 }
 
-__global__ void pass_begin_kernel(GateState gs, int n_blocks) {
-  for (int b = threadIdx.x; b < n_blocks; b += blockDim.x) {
-    gs.rec_dec[b] = 2;  // forced unless a decision kernel evaluates the block
-    gs.rec_s[b] = __builtin_nanf("");
-    gs.rec_d[b] = __builtin_nanf("");
-    gs.rec_tau[b] = __builtin_nanf("");
-    gs.flags[b] = 0;
-  }
-}
-
 int grid_for(long long n, int per_block) {
   long long g = (n + per_block - 1) / per_block;
   if (g > 8192) g = 8192;
@@ -425,10 +426,10 @@ int grid_for(long long n, int per_block) {
 }  // namespace
 
 void launch_cond(const float* action, int temb_dim, int action_dim, float timestep, float* cond_silu,
-                 hipStream_t st) {
+                 const GateState& gs, int n_blocks, hipStream_t st) {
   CondArgs a;
   for (int i = 0; i < kMaxAction; ++i) a.action[i] = i < action_dim ? action[i] : 0.f;
-  cond_kernel<<<1, 256, 0, st>>>(a, temb_dim, action_dim, timestep, cond_silu);
+  cond_kernel<<<1, 256, 0, st>>>(a, temb_dim, action_dim, timestep, cond_silu, gs, n_blocks);
 }
 
 void launch_adaln(int dtype, const void* w_ada, const float* b_ada, const float* cond_silu, int rows_per_block,
@@ -518,10 +519,6 @@ void launch_read_cache(int dtype, const void* src, float* out, int H, int R, int
 
 void launch_fill_f32(float* p, float v, long long n, hipStream_t st) {
   fill_f32_kernel<<<grid_for(n, 256 * 4), 256, 0, st>>>(p, v, n);
-}
-
-void launch_pass_begin(const GateState& gs, int n_blocks, hipStream_t st) {
-  pass_begin_kernel<<<1, 256, 0, st>>>(gs, n_blocks);
 }
 
 }  // namespace xc

@@ -141,8 +141,9 @@ struct FpTables {
 };
 
 // ---- launchers (each enqueues on `st`) -----------------------------------
+// n_blocks > 0 (a denoising pass): also resets gs.flags and the records
 void launch_cond(const float* action, int temb_dim, int action_dim, float timestep, float* cond_silu,
-                 hipStream_t st);
+                 const GateState& gs, int n_blocks, hipStream_t st);
 void launch_adaln(int dtype, const void* w_ada, const float* b_ada, const float* cond_silu, int rows_per_block,
                   long long block_stride_w, int n_blocks, int dc, float* mod, hipStream_t st);
 // rhat / skip_out: when the skip flag is set, write skip_out = x + rhat
@@ -176,7 +177,6 @@ void launch_attention(int dtype, const void* q, const void* kring, const void* v
                       size_t ws_floats, int L, int Mpad, int Lcap, int Lk, int H, int D, float score_bound,
                       const int* flag, hipStream_t st);
 void launch_axpby(float a, const float* x, float b, const float* y, float* out, long long n, hipStream_t st);
-void launch_pass_begin(const GateState& gs, int n_blocks, hipStream_t st);
 // Gated evaluation, first launch: fingerprint of x against the (t, b) cache
 // and the refresh.  fp0 / fp1: the (t, b) fingerprint sets; with sel == null
 // the cached fingerprint is fp0 and is overwritten in place, otherwise it is
