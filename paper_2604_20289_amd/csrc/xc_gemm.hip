@@ -8,8 +8,9 @@
 // stage tiles go from global memory straight into LDS (buffer loads).
 //  * gemm_bf16_wide: one 8-wave workgroup per CU, 256 x 256 or 192 x 256
 //    tiles;
-//  * gemm_bf16_small: 4 waves, 64 x 64 to 192 x 128 tiles, one workgroup per
-//    CU with a deep stage ring or two with a shallow one.
+//  * gemm_bf16_small: 4 waves (8 at 64 x 64, two groups sharing each stage's slices),
+//    64 x 64 to 192 x 128 tiles, one workgroup per CU with a deep stage ring or
+//    two with a shallow one.
 // pick_tile chooses.
 // Both run the element-wise epilogues through tile_epilogue (software-
 // pipelined operand loads, range-checked buffer stores) and the QKV epilogue
@@ -544,16 +545,27 @@ __device__ __forceinline__ void qkv_epilogue(const EpiArgs& e, const f32x16 (&ac
 //   768 tokens, hidden 512: QKV 13.0 -> 10.1 us, output projection 10.7 ->
 //   8.4, MLP up 11.2 -> 8.4, MLP down 26.4 -> 14.1; 3510 tokens, hidden 768:
 //   QKV 31 -> 26, output 17.4 -> 14.5, MLP down 48.8 -> 31.0.
+// With G = 2 a second group of four waves owns the same tile and takes the
+// second half of every stage's four slices: with the CU to itself a stage is
+// one wave's chain of fragment reads and MFMA per SIMD, and two halve it.  The
+// groups' sums meet in LDS once, after the last stage.  Only 64 x 64 has two:
+// 768 x 512 x 2048 14.3 -> 13.0 us, a 768-token pass of 10 blocks 517 -> 505.
+// 128 x 128 with five slots is 2% faster by itself (3245 x 1024 x 4096 38.7 ->
+// 37.8) but a pass of such products 1% slower (459 -> 464); 192 x 128 with four
+// slots is slower (3510 x 3072 x 768 29.1 -> 31.9: its sums are 96 KB); the
+// others share their CU.
 // ---------------------------------------------------------------------------
-template <int MODE, int MT, int NT, int NS>
-__global__ __launch_bounds__(256, NS * (MT + NT) * 8 > 80 ? 1 : 2) void gemm_bf16_small(const bf16* __restrict__ A, const bf16* __restrict__ W,
-                                                          int M, int N, int K, EpiArgs e,
-                                                          const int* __restrict__ flag) {
+template <int MODE, int MT, int NT, int NS, int G>
+__global__ __launch_bounds__(256 * G, NS * (MT + NT) * 8 > 80 ? G : 2) void gemm_bf16_small(
+    const bf16* __restrict__ A, const bf16* __restrict__ W, int M, int N, int K, EpiArgs e,
+    const int* __restrict__ flag) {
   if (flag != nullptr && *flag) return;
   constexpr int BM = 64 * MT, BN = 64 * NT;
   constexpr int STAGE = (BM + BN) * WBK;  // bf16 elements of one stage slot: A rows, then W rows
   constexpr int MAIN_BYTES = NS * STAGE * 2;
-  constexpr int EPI_BYTES = MODE == EPI_QKV ? qkv_epi_bytes<BM, BN, NT>() : 0;
+  constexpr int SUM_BYTES = (G - 1) * MT * NT * 16 * 256 * 4;  // the second group's partial sums
+  constexpr int QKV_BYTES = MODE == EPI_QKV ? qkv_epi_bytes<BM, BN, NT>() : 0;
+  constexpr int EPI_BYTES = QKV_BYTES > SUM_BYTES ? QKV_BYTES : SUM_BYTES;
   constexpr int LDS_BYTES = MAIN_BYTES > EPI_BYTES ? MAIN_BYTES : EPI_BYTES;
   static_assert(LDS_BYTES <= 160 * 1024, "ring fits");
   __shared__ __attribute__((aligned(1024))) char lds[LDS_BYTES];
@@ -573,7 +585,7 @@ __global__ __launch_bounds__(256, NS * (MT + NT) * 8 > 80 ? 1 : 2) void gemm_bf1
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int wm = wave >> 1, wn = wave & 1;
+  const int grp = wave >> 2, wm = (wave >> 1) & 1, wn = wave & 1;
   const int hi = lane >> 5, lo = lane & 31;
   const bf16* Ab = A + (long long)m0 * K;
   const bf16* Wb = W + (long long)n0 * K;
@@ -586,24 +598,27 @@ __global__ __launch_bounds__(256, NS * (MT + NT) * 8 > 80 ? 1 : 2) void gemm_bf1
       for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
 
   const int KT = K / WBK;
-  // request i of a stage: rows 8I .. 8I+7, I = wave + 4i, of A (i < 2 MT) or
+  // request i of a stage: rows 8I .. 8I+7, I = wave + 4G i, of A (i < AREQ) or
   // W; lane l lands at row 8I + l/8, physical chunk l%8
-  constexpr int AREQ = 2 * MT, LOADS = 2 * MT + 2 * NT;
+  constexpr int AREQ = 2 * MT / G, WREQ = 2 * NT / G, LOADS = AREQ + WREQ;
+  static_assert(AREQ * G == 2 * MT && WREQ * G == 2 * NT, "whole requests per wave");
   const int drow = wave * 8 + (lane >> 3);
-  int goff[MT > NT ? 2 * MT : 2 * NT];
+  int goff[AREQ > WREQ ? AREQ : WREQ];
 #pragma unroll
-  for (int i = 0; i < (MT > NT ? 2 * MT : 2 * NT); ++i) {
-    const int row = drow + 32 * i;
+  for (int i = 0; i < (AREQ > WREQ ? AREQ : WREQ); ++i) {
+    const int row = drow + 32 * G * i;
     goff[i] = (row * K + swz8(row, lane & 7) * 8) * 2;
   }
   auto request = [&](int kt, int slot, int i) __attribute__((always_inline)) {
-    bf16* dst = sbuf + slot * STAGE + (i < AREQ ? wave + 4 * i : BM / 8 + wave + 4 * (i - AREQ)) * 512;
+    bf16* dst = sbuf + slot * STAGE + (i < AREQ ? wave + 4 * G * i : BM / 8 + wave + 4 * G * (i - AREQ)) * 512;
     if (i < AREQ) dma16(Ab + kt * WBK, goff[i], dst);
     else dma16(Wb + kt * WBK, goff[i - AREQ], dst);
   };
-  int foff[4];
+  // the group's slices of a stage: SL grp .. SL grp + SL - 1
+  constexpr int SL = 4 / G;
+  int foff[SL];
 #pragma unroll
-  for (int kk = 0; kk < 4; ++kk) foff[kk] = lo * WBK + swz8(lo, 2 * kk + hi) * 8;
+  for (int kk = 0; kk < SL; ++kk) foff[kk] = lo * WBK + swz8(lo, 2 * (SL * grp + kk) + hi) * 8;
 #pragma unroll
   for (int k = 0; k < NS; ++k)
     if (k < KT) {
@@ -642,7 +657,7 @@ __global__ __launch_bounds__(256, NS * (MT + NT) * 8 > 80 ? 1 : 2) void gemm_bf1
   // every fragment of the stage is in registers; stage kt + 1 has landed once
   // at most `left` stages are still in flight; the slot goes to stage kt + NS,
   // requested over the last slice and the next step's first three.
-  constexpr int Q = (LOADS + 3) / 4;
+  constexpr int Q = (LOADS + SL - 1) / SL;
   auto cut = [](int i) { return i * Q < LOADS ? i * Q : LOADS; };
   int s = 0, prev = 0;
   int kt = 0;
@@ -650,9 +665,8 @@ __global__ __launch_bounds__(256, NS * (MT + NT) * 8 > 80 ? 1 : 2) void gemm_bf1
     const int s1 = s + 1 == NS ? 0 : s + 1;
     // the rest of stage kt + NS - 1 goes to the previous step's slot
     const int rest = kt > 0 ? kt + NS - 1 : -1;
-    slice(0, s, 1, rest, prev, cut(1), cut(2));
-    slice(1, s, 2, rest, prev, cut(2), cut(3));
-    slice(0, s, 3, rest, prev, cut(3), LOADS);
+#pragma unroll
+    for (int i = 1; i < SL; ++i) slice((i - 1) & 1, s, i, rest, prev, cut(i), i + 1 < SL ? cut(i + 1) : LOADS);
     XC_WAIT((NS - 2) * LOADS, 0);
     lds_barrier();
     slice(1, s1, 0, kt + NS, s, 0, cut(1));
@@ -665,8 +679,8 @@ __global__ __launch_bounds__(256, NS * (MT + NT) * 8 > 80 ? 1 : 2) void gemm_bf1
   for (; kt < KT; ++kt) {
     const int s1 = s + 1 == NS ? 0 : s + 1;
     slice(0, s, 1, first ? rest : -1, prev, cut(1), LOADS);
-    slice(1, s, 2, -1, 0, 0, 0);
-    slice(0, s, 3, -1, 0, 0, 0);
+#pragma unroll
+    for (int i = 2; i < SL; ++i) slice((i - 1) & 1, s, i, -1, 0, 0, 0);
     const int left = KT - 2 - kt;  // stages after the next one
     if (left >= NS - 2 && NS > 2) { XC_WAIT((NS - 2) * LOADS, 0); }
     else if (left >= 3 && NS > 5) { XC_WAIT(3 * LOADS, 0); }
@@ -680,6 +694,28 @@ __global__ __launch_bounds__(256, NS * (MT + NT) * 8 > 80 ? 1 : 2) void gemm_bf1
   }
   XC_WAIT(0, 0);  // the epilogue may reuse the LDS
   lds_barrier();
+  if constexpr (G == 2) {
+    // the second group's sums go to the first one, which runs the epilogue (a
+    // wave that has ended no longer counts in the workgroup's barriers)
+    float* sum = reinterpret_cast<float*>(lds) + (tid & 255);
+    if (grp == 1) {
+#pragma unroll
+      for (int i = 0; i < MT; ++i)
+#pragma unroll
+        for (int j = 0; j < NT; ++j)
+#pragma unroll
+          for (int r = 0; r < 16; ++r) sum[((i * NT + j) * 16 + r) * 256] = acc[i][j][r];
+    }
+    __syncthreads();
+    if (grp == 1) return;
+#pragma unroll
+    for (int i = 0; i < MT; ++i)
+#pragma unroll
+      for (int j = 0; j < NT; ++j)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[i][j][r] += sum[((i * NT + j) * 16 + r) * 256];
+    if constexpr (MODE == EPI_QKV) __syncthreads();  // its epilogue writes the same LDS
+  }
 
   // accumulator element (mt, nt, g, r): tile row wm*MT*32 + mt*32 + g*8 + hi*4 + r,
   // tile column wn*NT*32 + nt*32 + lo
@@ -994,8 +1030,8 @@ long long rounds_of(int M, int N, int BM, int BN, int slots) {
 // the launch, the first stage's latency and the epilogue).  Small tiles run one
 // workgroup per CU with a deep ring or two with a shallow one; a shallow 64 x
 // 128 tile with its CU to itself takes its own line.
-//   768 x 512 x 2048 (MLP down): 64 x 64 14.1 us, 64 x 128 15.5, 128 x 128 21.6
-//   3245 x 1024 x 4096: 64 x 128 43.6, 128 x 128 deep 41.3, 192 x 128 58.9
+//   768 x 512 x 2048 (MLP down): 64 x 64 13.0 us, 64 x 128 15.4, 128 x 128 20.4
+//   3245 x 1024 x 4096: 64 x 128 44.1, 128 x 128 deep 38.9, 192 x 128 56.9
 //   3510 x 2304 x 768 (QKV): 64 x 128 30.6, 128 x 128 shallow 26.1
 //   7020 x 1536 x 6144: 128 x 128 172, 192 x 128 142, 192 x 256 133, 256 x 256 161
 //   12096 x 6144 x 2048 (QKV): 256 x 256 275 (5 rounds), 192 x 256 364 (6 rounds)
@@ -1032,12 +1068,12 @@ int pick_tile(int M, int N, int K, int C) {
   return best;
 }
 
-template <int MODE, int MT, int NT, int NS>
+template <int MODE, int MT, int NT, int NS, int G>
 void launch_small_tile(const void* A, const void* W, int M, int N, int K, const EpiArgs& e, const int* flag,
                        hipStream_t st) {
   const int tiles = ((M + 64 * MT - 1) / (64 * MT)) * (N / (64 * NT));
   const int grid = (tiles + kXcd - 1) / kXcd * kXcd;
-  gemm_bf16_small<MODE, MT, NT, NS><<<grid, 256, 0, st>>>((const bf16*)A, (const bf16*)W, M, N, K, e, flag);
+  gemm_bf16_small<MODE, MT, NT, NS, G><<<grid, 256 * G, 0, st>>>((const bf16*)A, (const bf16*)W, M, N, K, e, flag);
 }
 
 template <int MODE, int BM, bool AAHEAD>
@@ -1056,13 +1092,13 @@ void launch_mode(int dtype, const void* A, const void* W, int M, int N, int K, c
       constexpr bool qkv = MODE == EPI_QKV;
       switch (pick_tile(M, N, K, qkv ? e.H * e.D : 0)) {
         case kT64x64:
-          if constexpr (!qkv) launch_small_tile<MODE, 1, 1, 8>(A, W, M, N, K, e, flag, st);
+          if constexpr (!qkv) launch_small_tile<MODE, 1, 1, 8, 2>(A, W, M, N, K, e, flag, st);
           break;
-        case kT64x128: launch_small_tile<MODE, 1, 2, 3>(A, W, M, N, K, e, flag, st); break;
-        case kT128x128deep: launch_small_tile<MODE, 2, 2, 5>(A, W, M, N, K, e, flag, st); break;
-        case kT128x128: launch_small_tile<MODE, 2, 2, 2>(A, W, M, N, K, e, flag, st); break;
-        case kT192x128deep: launch_small_tile<MODE, 3, 2, 4>(A, W, M, N, K, e, flag, st); break;
-        case kT192x128: launch_small_tile<MODE, 3, 2, 2>(A, W, M, N, K, e, flag, st); break;
+        case kT64x128: launch_small_tile<MODE, 1, 2, 3, 1>(A, W, M, N, K, e, flag, st); break;
+        case kT128x128deep: launch_small_tile<MODE, 2, 2, 5, 1>(A, W, M, N, K, e, flag, st); break;
+        case kT128x128: launch_small_tile<MODE, 2, 2, 2, 1>(A, W, M, N, K, e, flag, st); break;
+        case kT192x128deep: launch_small_tile<MODE, 3, 2, 4, 1>(A, W, M, N, K, e, flag, st); break;
+        case kT192x128: launch_small_tile<MODE, 3, 2, 2, 1>(A, W, M, N, K, e, flag, st); break;
         case kT256x256: launch_wide<MODE, 256, true>(A, W, M, N, K, e, flag, st); break;
         case kT192x256: launch_wide<MODE, 192, false>(A, W, M, N, K, e, flag, st); break;
       }

@@ -19,6 +19,7 @@ pytestmark = pytest.mark.gpu
 #   h768-L16000: 192 x 256, K = 768; the same
 #   h2048-L6100: 192 x 256, K = 2048 / 64 x 64 / 256 x 256, K = 128; 192 x 256
 #   h640-L5000: 128 x 128 with five slots, K = 640 and 1280, 128 x 128 with two; 192 x 128
+#   h1024-L1100: 128 x 128 with five slots, K = 1024, also in the QKV product
 #   h256-L70: 64 x 128 and 64 x 64, K = 256 (four stages) and 1024
 SHAPES = {
     "h384-L16000": (384, 3, 384, (1, 1, 125, 128)),
@@ -26,6 +27,7 @@ SHAPES = {
     "h768-L16000": (768, 6, 768, (1, 1, 125, 128)),
     "h2048-L6100": (2048, 16, 128, (1, 1, 61, 100)),
     "h640-L5000": (640, 5, 1280, (2, 1, 50, 50)),
+    "h1024-L1100": (1024, 8, 1024, (1, 1, 44, 25)),
     "h256-L70": (256, 2, 1024, (1, 1, 7, 10)),
 }
 
