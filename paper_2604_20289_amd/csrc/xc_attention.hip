@@ -943,8 +943,13 @@ int resident_attention_groups() {
 // Key splits per item.  Estimated time in key-tile steps of one resident
 // workgroup: rounds * (tiles per unit + 4 for the unit's prologue and
 // epilogue) + 4 S items / (resident workgroups) for the merge (fitted to
-// measured split sweeps on the multi-camera shapes, where it picks S = 3),
-// over S <= 16 with chunks of at least 2 tiles: few items take more splits
+// measured split sweeps on the multi-camera shapes, where it picks S = 3) + 5
+// for the merge's launch, which a skipped block also pays (1.8 us), over S <=
+// 16 with chunks of at least 2 tiles.  Up to 7 key tiles stay whole: 400
+// tokens, 8 heads of 64, 5 / 7 / 8 tiles 13.6 / 14.9 / 15.6 us whole, 14.0 /
+// 14.6 / 14.6 in three splits; 12 heads of 128 19.0 / 20.9 / 22.1 and 18.4 /
+// 19.4 / 19.5; 4186 tokens, 8 heads of 128 (136 items, past one round when
+// split) 20.5 / 22.9 / 24.4 and 32 / 36 / 37.  Few items take more splits
 // (768 tokens, 8 heads, 3072 keys, 24 items: 10 splits 19.3 us, 5 splits 21.4,
 // none 47; 300 tokens, 2 heads, 600 keys: 5 splits 18.3 us, 2 splits 21.0); only split
 // counts whose partials fit in cap_floats workspace floats are considered
@@ -959,7 +964,7 @@ int attention_splits(int L, int Lk, int H, int D, size_t cap_floats) {
     if (s > 1 && (size_t)items * s * (size_t)piece_floats(D) > cap_floats) break;
     const long long units = (long long)items * s;
     const long long rounds = (units + slots - 1) / slots;
-    const double cost = (double)rounds * ((double)NT / s + 4.0) + (s > 1 ? 4.0 * s * items / slots : 0.0);
+    const double cost = (double)rounds * ((double)NT / s + 4.0) + (s > 1 ? 5.0 + 4.0 * s * items / slots : 0.0);
     if (cost < best_cost - 1e-9) {
       best_cost = cost;
       best = s;
