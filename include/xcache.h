@@ -357,8 +357,8 @@ xc_status xc_kernel_times(xc_handle* h, int32_t kind, int64_t* launches, double*
 xc_status xc_mfma_rate(int32_t shape, int32_t random_operands, void* stream, double* tflops);
 
 /* Measurement aid, not a step of the method: the rate of the global -> LDS
- * request stream (global_load_lds_dwordx4) that the GEMMs stage their
- * operands with, as a function of the row segment one request fetches.
+ * request stream (global_load_lds_dwordx4: 16 bytes per lane straight into
+ * LDS, as the GEMMs stage their operands), as a function of the row segment one request fetches.
  * 1008 workgroups (two per CU) each stream 24 KB stages of the rows of one
  * of 28 shared row blocks (33 MB in all, as the M-tiles of a GEMM share
  * their rows) through a 3-slot LDS ring two stages ahead, with no

@@ -8,9 +8,9 @@
 // stage tiles go from global memory straight into LDS (buffer loads).
 //  * gemm_bf16_wide: one 8-wave workgroup per CU, 256 x 256 or 192 x 256
 //    tiles;
-//  * gemm_bf16_small: 4 waves (8 at 64 x 64, two groups sharing each stage's slices),
-//    64 x 64 to 192 x 128 tiles, one workgroup per CU with a deep stage ring or
-//    two with a shallow one.
+//  * gemm_bf16_small: 4 waves (8 at 64 x 64, two groups sharing each stage's
+//    slices), 64 x 64 to 192 x 128 tiles, one workgroup per CU with a deep stage
+//    ring or two with a shallow one.
 // pick_tile chooses.
 // Both run the element-wise epilogues through tile_epilogue (software-
 // pipelined operand loads, range-checked buffer stores) and the QKV epilogue
@@ -729,8 +729,8 @@ __global__ __launch_bounds__(256 * G, NS * (MT + NT) * 8 > 80 ? G : 2) void gemm
 // ---------------------------------------------------------------------------
 // Wide bf16 MFMA GEMM: one workgroup of 8 waves per CU owns a BM x 256 tile,
 // its waves in a 2 x 4 arrangement: 256 x 256 tiles of 128 x 64 (4 x 2
-// accumulators each), 192 x 256 of 96 x 64 (3 x 2).  Stages are 64 deep: every DMA request fetches 128 contiguous bytes of a row (a whole cache
-// line; the request stream measures 14.6 TB/s with the 64-byte segments of
+// accumulators each), 192 x 256 of 96 x 64 (3 x 2).  Stages are 64 deep: every
+// DMA request fetches 128 contiguous bytes of a row (a whole cache line; the request stream measures 14.6 TB/s with the 64-byte segments of
 // 32-deep stages against 24.5 TB/s with 128-byte ones, xc_lds_dma_rate).
 // LDS rows are 128 bytes with their 16-byte chunks XOR-swizzled (swz8) so the
 // 32 rows a half-wave reads at one chunk position fall in distinct banks.
