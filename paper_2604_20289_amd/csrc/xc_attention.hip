@@ -433,9 +433,14 @@ __global__ __launch_bounds__(64 * kWaves, 1) void attn_bf16_kernel(const bf16* _
 //
 // The MFMAs are asm statements because the compiler otherwise keeps S in
 // AGPRs and copies it out for the exponentials.  It does not see them as
-// MFMAs: settle() gives the wait states that a VALU read of an MFMA result
-// needs where no 16 other MFMAs lie in between, pin() those between a
-// register copy and an MFMA.
+// MFMAs, so the wait states around them are written here.  In the key loop
+// the slots' scheduling barriers keep the distances: between the last MFMA on
+// a score tile and its first exponential lie the 16 MFMAs (8 at d = 64) of
+// P V with their VALU work, between a probability and its MFMA the slots of
+// K Q^T.  Everywhere else settle() comes between an MFMA and the VALU reads
+// of its result, ready() and pin() between VALU writes and an MFMA that reads
+// them; each ties the registers it stands for, because the scheduler moves
+// register arithmetic freely past a wait that names none.
 template <int D>
 __global__ __launch_bounds__(64 * kBWaves, 1) void attn_bounded_kernel(const bf16* __restrict__ Q, const bf16* __restrict__ Kc,
                                                               const bf16* __restrict__ Vt, bf16* __restrict__ O, int L,
@@ -622,7 +627,13 @@ __global__ __launch_bounds__(64 * kBWaves, 1) void attn_bounded_kernel(const bf1
   auto none = [](int) __attribute__((always_inline)) {};
   // MFMA results that VALU instructions read need up to 19 wait states after
   // the last MFMA; the compiler does not see the MFMAs in the asm
-  auto settle = [&]() __attribute__((always_inline)) { asm volatile("s_nop 15\n s_nop 7" ::: "memory"); };
+  auto settle = [&](f32x16 (&s)[2]) __attribute__((always_inline)) {
+    asm volatile("s_nop 15\n s_nop 7" : "+v"(s[0]), "+v"(s[1]));
+  };
+  // ... registers that VALU instructions wrote need 2 before an MFMA reads them
+  auto ready = [&](u32x4 (&pk)[2][2]) __attribute__((always_inline)) {
+    asm volatile("s_nop 3" : "+v"(pk[0][0]), "+v"(pk[0][1]), "+v"(pk[1][0]), "+v"(pk[1][1]));
+  };
   // ... and register copies of the accumulators, where the compiler makes
   // any, must not directly precede an MFMA that accumulates on them
   auto pin = [&]() __attribute__((always_inline)) {
@@ -645,7 +656,7 @@ __global__ __launch_bounds__(64 * kBWaves, 1) void attn_bounded_kernel(const bf1
       else if (i < KB + VB) dma16(vbase, vg[i - KB], vdst + (wave + NW * (i - KB)) * 512);
     };
     step(kcur, 1, vprev, 1, knext, 0, sb, sa, pb, pa, !first, dma);
-    if (first) pin(), settle();
+    if (first) pin(), settle(sb);
     step(knext, 0, vcur, 0, knext, 1, sa, sb, pa, pb, true, none);
     XC_WAIT_VMCNT0();
     tile_barrier();
@@ -671,7 +682,7 @@ __global__ __launch_bounds__(64 * kBWaves, 1) void attn_bounded_kernel(const bf1
           asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+v"(sn[g]) : "v"(a), "v"(qf[g][i]));
       }
     }
-    settle();
+    settle(sn);
   };
   auto probs = [&](const f32x16 (&s)[2], u32x4 (&pk)[2][2]) __attribute__((always_inline)) {
 #pragma unroll
@@ -706,16 +717,22 @@ __global__ __launch_bounds__(64 * kBWaves, 1) void attn_bounded_kernel(const bf1
   probs(sa, pa);
   if (k0 < jl) {
     pin();
+    ready(pb);
     pv_half(pb, vp, 1);
   }
   qk_half(sb, kt, 1);
   mask(sb, jl, 1);
   probs(sb, pb);
-  settle();
   pin();
+  ready(pa);
+  ready(pb);
   pv_half(pa, vt, 0);
   pv_half(pb, vt, 1);
-  settle();
+  asm volatile("s_nop 15\n s_nop 7");
+#pragma unroll
+  for (int g = 0; g < 2; ++g)
+#pragma unroll
+    for (int i = 0; i < DT; ++i) asm volatile("" : "+a"(oacc[g][i]));
 
   const int C = H * D;
   typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
