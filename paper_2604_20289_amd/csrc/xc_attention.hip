@@ -70,10 +70,6 @@ constexpr int kWaves = 8;            // waves per attention workgroup
 constexpr int kQT = 32 * kWaves;     // queries per attention workgroup
 constexpr int kBWaves = kQT / 64;    // waves of the bounded kernel's workgroup
 
-// Largest bound on |score| (log2 units) for which the softmax needs no
-// running maximum (launch_attention).
-constexpr float kMaxScoreBound = 64.0f;
-
 // Workspace floats of one (item, key split) piece: the piece's output
 // normalised by its own softmax sum, bf16 [kQT][D], then its running max and
 // sum, float [kQT] each.
@@ -407,7 +403,7 @@ __global__ __launch_bounds__(64 * kWaves, 1) void attn_bf16_kernel(const bf16* _
   }
 }
 
-// Attention whose scores are bounded (launch_attention).  2^s then needs no
+// Attention whose scores are bounded (attention_bounded).  2^s then needs no
 // running maximum: the output accumulators are touched by nothing but MFMAs
 // and sit in AGPRs, and a wave has registers for 64 queries.  A workgroup is
 // 4 waves (one per SIMD); the two 32-query groups of a wave share every K /
@@ -996,13 +992,9 @@ size_t attention_workspace_floats(int L, int Lk, int H, int D) {
   return (size_t)H * ((L + kQT - 1) / kQT) * s * (size_t)piece_floats(D);
 }
 
-// Score bound: with |s| <= 64 (log2 units) probabilities 2^s lie in
-// [2^-64, 2^64], their sums over at most 2^24 keys and P.V stay finite for
-// |v| < 2^39, and nothing that matters to a sum underflows, so no maximum is
-// subtracted: numerator and denominator carry the same relative errors as
-// with one.  Gains of 1 give a bound of 16.6 (d = 128); past 64 (gain
-// products over 3.8) the running-maximum kernel keeps p <= 2^8 whatever the
-// scores.  Its time at the shape above is 823 us.
+// bounded: no running maximum (the limits and their reasons:
+// attention_bounded); otherwise the running-maximum kernel keeps p <= 2^8
+// whatever the scores.  Its time at the shape above is 823 us.
 //
 // bf16 requirements (checked by the caller): D in {64, 128}; Q has Mpad >=
 // roundup(L, 256) rows per head; the caches have Lcap >= roundup(Lk, 64) rows,
@@ -1011,14 +1003,12 @@ size_t attention_workspace_floats(int L, int Lk, int H, int D) {
 // split is limited to what fits: attention_workspace_floats(L, Lk, H, D)
 // floats allow the unconstrained choice).
 void launch_attention(int dtype, const void* q, const void* kc, const void* vt, void* o, float* ws, size_t ws_floats,
-                      int L, int Mpad, int Lcap, int Lk, int H, int D, float score_bound, const int* flag,
-                      hipStream_t st) {
+                      int L, int Mpad, int Lcap, int Lk, int H, int D, bool bounded, const int* flag, hipStream_t st) {
   if (dtype == 1) {
     const int n_qt = (L + kQT - 1) / kQT;
     const int n_split = attention_splits(L, Lk, H, D, ws != nullptr ? ws_floats : 0);
     const int units = H * n_split * n_qt;
     const int grid = (units + kXcds - 1) / kXcds * kXcds;
-    const bool bounded = score_bound <= kMaxScoreBound;  // false for a NaN bound
 #define XC_ATTN(DD)                                                                                                \
   do {                                                                                                             \
     if (bounded)                                                                                                   \

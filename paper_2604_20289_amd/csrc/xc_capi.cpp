@@ -39,6 +39,7 @@
 #include <vector>
 
 #include "xc_internal.h"
+#include "xc_rules.h"
 #include "xcache.h"
 
 using namespace xc;
@@ -113,8 +114,12 @@ struct xc_handle {
   void* wo_c = nullptr; float* bo_c = nullptr; float* ln3_shift = nullptr; float* ln3_scale = nullptr;
   void* kc_c = nullptr; void* vt_c = nullptr; void* cond_act = nullptr; float* cond_kv = nullptr;
   float* ones = nullptr;
-  // per block, an upper bound of the (cross-)attention's |score| in log2 units
+  // per block, what bounds the (cross-)attention's scores (log2 units) and
+  // values: the gains, the rows of W_ada (shift and scale of the first
+  // LayerNorm) and of Wv, the conditioning and the condition tokens
   std::vector<float> score_bound, score_bound_c;
+  std::vector<RowBound> mod_rows, v_rows, v_rows_c;
+  double cond_max = 1.0, token_max = 0.0;
   // gate global channel from the MLP-down epilogue (bf16 models whose cameras
   // all have >= 32 tokens): partials, 32-row-block tables, per-pass input sums
   // and per-(t, b) residual sums
@@ -446,27 +451,21 @@ P* wptr(void* base, size_t elems_before, size_t esz) {
   return reinterpret_cast<P*>(reinterpret_cast<char*>(base) + elems_before * esz);
 }
 
-// The softmax scale 1 / sqrt(d) in log2 units; bf16 models fold it into the
-// stored queries.
-float softmax_scale(int D) { return 1.4426950408889634f / sqrtf((float)D); }
+// Which attention kernel the (cross-)attention of block b takes (bf16 models;
+// see attention_bounded).
+bool self_bounded(const xc_handle* h, int b, long long Lk) {
+  return attention_bounded(h->score_bound[b],
+                           self_value_bound(h->mod_rows[b], h->v_rows[b], h->C, h->Dc, h->cond_max), Lk);
+}
 
-// Upper bound of |q . k| / sqrt(d) in log2 units from the RMSNorm gains: a
-// normalised head vector has norm at most sqrt(d), so |q . k| <= d max_i
-// |gq_i gk_i|; a rotation mixes the dimensions of a pair, so the maximum then
-// is taken per pair.  2% cover the rounding of q and k to bf16 (2^-8 each).
-float qk_score_bound(const float* gq, const float* gk, int D, bool rope) {
-  const int step = rope ? 2 : 1;
-  float most = 0.f;
-  for (int i = 0; i + step <= D; i += step) {
-    float a = 0.f, b = 0.f;
-    for (int j = i; j < i + step; ++j) {
-      if (!std::isfinite(gq[j]) || !std::isfinite(gk[j])) return INFINITY;
-      a = std::max(a, std::fabs(gq[j]));
-      b = std::max(b, std::fabs(gk[j]));
-    }
-    most = std::max(most, a * b);
-  }
-  return 1.02f * (float)D * softmax_scale(D) * most;
+bool cross_bounded(const xc_handle* h, int b) {
+  return attention_bounded(h->score_bound_c[b], cross_value_bound(h->v_rows_c[b], h->C, h->token_max), h->n_cond);
+}
+
+// The largest magnitude a pass's conditioning has had since the last reset:
+// the visible window holds values of earlier generations too.
+void note_action(xc_handle* h, const float* a) {
+  for (int i = 0; i < h->A; ++i) h->cond_max = std::max(h->cond_max, (double)std::fabs(a[i]));
 }
 
 // Cross-attention layer of block b on x1 (in place): affine LayerNorm, q
@@ -507,7 +506,7 @@ void cross_attention(xc_handle* h, int b, const int* flag, const PassWs& ws) {
     launch_attention(h->dtype, h->q, wptr<void>(h->kc_c, (size_t)b * H * h->Lcap_c * D, esz),
                      wptr<void>(h->vt_c, (size_t)b * H * h->Lcap_c * D, esz), h->o, ws.attn, ws.attn_floats, L,
                      (int)h->Mpad,
-                     (int)h->Lcap_c, h->n_cond, H, D, h->score_bound_c[b], flag, h->st);
+                     (int)h->Lcap_c, h->n_cond, H, D, cross_bounded(h, b), flag, h->st);
   }
   {
     Prof p(h, XC_KERN_CROSS_O);
@@ -587,7 +586,7 @@ void compute_block(xc_handle* h, int b, const float* x, float* out, const int* f
   {
     Prof p(h, XC_KERN_ATTENTION);
     launch_attention(h->dtype, h->q, kc_b, vt_b, h->o, ws.attn, ws.attn_floats, L, (int)h->Mpad, (int)h->Lcap, (int)Lk,
-                     H, D, h->score_bound[b], flag, h->st);
+                     H, D, self_bounded(h, b, Lk), flag, h->st);
   }
   {
     Prof p(h, XC_KERN_GEMM_OPROJ);
@@ -800,6 +799,7 @@ void reset_state(xc_handle* h) {
   h->any_forward = false;
   h->have_action_prev = false;
   h->have_action_cur = false;
+  h->cond_max = 1.0;
 }
 
 void free_all(xc_handle* h) {
@@ -848,11 +848,17 @@ void init_device(xc_handle* h, const float* w) {
   const size_t CC = (size_t)C * C;
   for (int b = 0; b < B; ++b) {
     upload(h, w + off, (size_t)6 * C * Dc, wptr<void>(h->w_ada, (size_t)b * 6 * C * Dc, esz), bf, stage);
+    h->mod_rows.emplace_back();
+    if (bf) h->mod_rows[b].add(w + off, w + off + (size_t)6 * C * Dc, (size_t)2 * C, Dc);
     off += (size_t)6 * C * Dc;
     upload(h, w + off, (size_t)6 * C, h->b_ada + (size_t)b * 6 * C, false, stage);
     off += (size_t)6 * C;
     for (int part = 0; part < 3; ++part) {  // Wq, bq, Wk, bk, Wv, bv
       upload(h, w + off, CC, wptr<void>(h->wqkv, (size_t)b * 3 * CC + part * CC, esz), bf, stage);
+      if (part == 2) {
+        h->v_rows.emplace_back();
+        if (bf) h->v_rows[b].add(w + off, w + off + CC, C, C);
+      }
       off += CC;
       upload(h, w + off, C, h->bqkv + (size_t)b * 3 * C + part * C, false, stage);
       off += C;
@@ -884,6 +890,10 @@ void init_device(xc_handle* h, const float* w) {
       off += C;
       for (int part = 0; part < 3; ++part) {  // Wq_c, bq_c, Wk_c, bk_c, Wv_c, bv_c
         upload(h, w + off, CC, wptr<void>(h->wqkv_c, (size_t)b * 3 * CC + part * CC, esz), bf, stage);
+        if (part == 2) {
+          h->v_rows_c.emplace_back();
+          if (bf) h->v_rows_c[b].add(w + off, w + off + CC, C, C);
+        }
         off += CC;
         upload(h, w + off, C, h->bqkv_c + (size_t)b * 3 * C + part * C, false, stage);
         off += C;
@@ -998,6 +1008,7 @@ xc_status forward_pass(xc_handle* h, int32_t step, float timestep, const float* 
   try {
     XC_HIP(hipSetDevice(h->device));
     fix_action(h, action_host);
+    note_action(h, action_host);
     const xc_gate_config& g = h->g;
     const bool forced_all = !g.enabled || h->n < g.warmup || (flags & XC_FORCE_FULL) ||
                             (step == 0 && g.step0_mode == XC_STEP0_FORCE);
@@ -1164,6 +1175,7 @@ xc_status xc_kv_update(xc_handle* h, float timestep, const float* action_host, c
   if (action_changed(h, action_host)) return XC_ERR_STATE;
   try {
     XC_HIP(hipSetDevice(h->device));
+    note_action(h, action_host);
     pass_conditioning(h, timestep, action_host, false);
     const long long kv_off = (h->n % h->Wkv) * h->L;
     const long long Lk = std::min<long long>(h->n + 1, h->Wkv) * h->L;
@@ -1196,8 +1208,15 @@ xc_status xc_set_condition(xc_handle* h, const float* cond_host, int32_t n_token
   if (n_tokens < 1 || n_tokens > h->Mc) return XC_ERR_INVALID_ARG;
   const int C = h->C, H = h->H, D = h->D;
   const size_t count = (size_t)n_tokens * C;
-  for (size_t i = 0; i < count; ++i)
-    if (!std::isfinite(cond_host[i])) return XC_ERR_INVALID_ARG;
+  int32_t most = 0;  // the largest magnitude: the bits of non-negative floats order as integers
+  for (size_t i = 0; i < count; ++i) {
+    int32_t bits;
+    std::memcpy(&bits, cond_host + i, sizeof(bits));
+    most = std::max(most, bits & 0x7fffffff);
+  }
+  if (most >= 0x7f800000) return XC_ERR_INVALID_ARG;  // an infinity or a NaN
+  float token_max;
+  std::memcpy(&token_max, &most, sizeof(token_max));
   try {
     XC_HIP(hipSetDevice(h->device));
     const bool bf = h->dtype == XC_BF16;
@@ -1235,6 +1254,7 @@ xc_status xc_set_condition(xc_handle* h, const float* cond_host, int32_t n_token
     if (check_launch() != XC_OK) throw Fail{XC_ERR_HIP};
     XC_HIP(hipStreamSynchronize(h->st));
     h->n_cond = n_tokens;
+    h->token_max = token_max;
   } catch (const Fail& f) {
     h->sticky = true;
     return f.s;

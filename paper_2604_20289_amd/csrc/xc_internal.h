@@ -171,10 +171,10 @@ void launch_rope_table(float2* tab, const RopeArgs& r, int n_slots, const int* s
 size_t attention_workspace_floats(int L, int Lk, int H, int D);
 // ws: ws_floats floats of workspace; the key split is chosen among those
 // whose partials fit (none: no split).  bf16: the queries are already scaled
-// by log2(e) / sqrt(D) (EpiArgs::q_scale); score_bound: an upper bound of
-// |q . k| in those units (infinity: none known).
+// by log2(e) / sqrt(D) (EpiArgs::q_scale); bounded: the scores and values are
+// within the limits of attention_bounded.
 void launch_attention(int dtype, const void* q, const void* kring, const void* vtring, void* o, float* ws,
-                      size_t ws_floats, int L, int Mpad, int Lcap, int Lk, int H, int D, float score_bound,
+                      size_t ws_floats, int L, int Mpad, int Lcap, int Lk, int H, int D, bool bounded,
                       const int* flag, hipStream_t st);
 void launch_axpby(float a, const float* x, float b, const float* y, float* out, long long n, hipStream_t st);
 // Gated evaluation, first launch: fingerprint of x against the (t, b) cache

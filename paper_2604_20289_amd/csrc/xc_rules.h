@@ -1,0 +1,86 @@
+// Host-side rules of the dispatch: plain arithmetic on sizes and weights,
+// without HIP, so that they can be compiled and checked on any host.
+#pragma once
+
+#include <algorithm>
+#include <cmath>
+#include <cstddef>
+
+namespace xc {
+
+// The softmax scale 1 / sqrt(d) in log2 units; bf16 models fold it into the
+// stored queries.
+inline float softmax_scale(int D) { return 1.4426950408889634f / sqrtf((float)D); }
+
+// Upper bound of |q . k| / sqrt(d) in log2 units from the RMSNorm gains: a
+// normalised head vector has norm at most sqrt(d), so |q . k| <= d max_i
+// |gq_i gk_i|; a rotation mixes the dimensions of a pair, so the maximum then
+// is taken per pair.  2% cover the rounding of q and k to bf16 (2^-8 each).
+// Infinity where a gain is not finite.
+inline float qk_score_bound(const float* gq, const float* gk, int D, bool rope) {
+  const int step = rope ? 2 : 1;
+  float most = 0.f;
+  for (int i = 0; i + step <= D; i += step) {
+    float a = 0.f, b = 0.f;
+    for (int j = i; j < i + step; ++j) {
+      if (!std::isfinite(gq[j]) || !std::isfinite(gk[j])) return INFINITY;
+      a = std::max(a, std::fabs(gq[j]));
+      b = std::max(b, std::fabs(gk[j]));
+    }
+    most = std::max(most, a * b);
+  }
+  return 1.02f * (float)D * softmax_scale(D) * most;
+}
+
+// Upper bound of an affine map's outputs |w_r . h + b_r| over its rows r:
+// `norm` the largest 2-norm of a row, `bias` the largest |b_r|.  Rows with a
+// non-finite element make it infinite or NaN, which no rule accepts.
+struct RowBound {
+  double norm = 0, bias = 0;
+  void add(const float* w, const float* b, size_t rows, size_t cols) {
+    for (size_t r = 0; r < rows; ++r) {
+      double s[4] = {0, 0, 0, 0};
+      const float* p = w + r * cols;
+      size_t i = 0;
+      for (; i + 4 <= cols; i += 4)
+        for (int k = 0; k < 4; ++k) s[k] += (double)p[i + k] * p[i + k];
+      for (; i < cols; ++i) s[0] += (double)p[i] * p[i];
+      const double n = std::sqrt((s[0] + s[1]) + (s[2] + s[3])), a = std::fabs((double)b[r]);
+      norm = n > norm || std::isnan(n) ? n : norm;
+      bias = a > bias || std::isnan(a) ? a : bias;
+    }
+  }
+};
+
+// Largest |v| of a self-attention: v = Wv h + bv with h = LN(x) (1 + scale) +
+// shift, |LN(x)|_2 <= sqrt(C); the modulations are rows of W_ada SiLU(c) +
+// b_ada with |c_k| <= cond_max (at least 1, the timestep embedding), Dc
+// entries.  1% per factor covers the bf16 roundings.
+inline double self_value_bound(const RowBound& mod, const RowBound& v, int C, int Dc, double cond_max) {
+  const double m = 1.01 * (mod.norm * std::sqrt((double)Dc) * cond_max + mod.bias);
+  return 1.01 * (v.norm * 1.01 * std::sqrt((double)C) * (1 + 2 * m) + v.bias);
+}
+
+// ... and of a cross-attention over condition tokens with |cond| <= cond_max.
+inline double cross_value_bound(const RowBound& v, int C, double cond_max) {
+  return 1.01 * (v.norm * 1.01 * std::sqrt((double)C) * cond_max + v.bias);
+}
+
+// Attention without a running maximum (attn_bounded_kernel): probabilities are
+// 2^s, |s| <= score_bound (log2 units), values at most value_bound, and
+// numerator and denominator carry the same relative errors as with a maximum
+// subtracted as long as neither leaves the range of a float.
+// * score_bound <= 64: sums of probabilities do not.  Gains of 1 give 16.6 (d =
+//   128), gain products over 3.8 pass 64.
+// * the sum over Lk keys of 2^s |v| stays below 2^120, so no partial sum
+//   overflows where the running maximum (p <= 2^8) would not;
+// * the smallest products that matter, 2^-s |v| 2^-24, stay above 2^-126 for
+//   values down to 2^-10 of their bound (4 - 200 times what models store).
+// Ordinary models are far from both (|v| of 2^10, 48384 keys: 2^42 at a bound
+// of 16.6).  False for a bound that is NaN or infinite.
+inline bool attention_bounded(float score_bound, double value_bound, long long Lk) {
+  const double values = std::log2(value_bound);
+  return score_bound <= 64.0f && score_bound + std::log2((double)Lk) + values <= 120.0 && score_bound - values <= 92.0;
+}
+
+}  // namespace xc

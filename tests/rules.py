@@ -1,0 +1,48 @@
+"""The host-side dispatch rules (csrc/xc_rules.h), compiled with the host
+compiler and called through ctypes."""
+import ctypes
+import functools
+import os
+import subprocess
+import tempfile
+
+import numpy as np
+
+from paper_2604_20289_amd import build
+
+SHIM = r"""
+#include "xc_rules.h"
+using namespace xc;
+extern "C" {
+float score_bound(const float* gq, const float* gk, int D, int rope) { return qk_score_bound(gq, gk, D, rope != 0); }
+double self_bound(const float* w_ada, const float* b_ada, const float* wv, const float* bv, int C, int Dc, double cond_max) {
+  RowBound m, v;
+  m.add(w_ada, b_ada, (size_t)2 * C, Dc);
+  v.add(wv, bv, C, C);
+  return self_value_bound(m, v, C, Dc, cond_max);
+}
+double cross_bound(const float* wv, const float* bv, int C, double cond_max) {
+  RowBound v;
+  v.add(wv, bv, C, C);
+  return cross_value_bound(v, C, cond_max);
+}
+int bounded(float score, double value, long long Lk) { return attention_bounded(score, value, Lk); }
+}
+"""
+
+
+@functools.lru_cache(None)
+def lib():
+    d = tempfile.mkdtemp(prefix="xc_rules_")
+    src, so = os.path.join(d, "shim.cpp"), os.path.join(d, "shim.so")
+    with open(src, "w") as f:
+        f.write(SHIM)
+    subprocess.run(["g++", "-std=c++17", "-O2", "-Wall", "-Werror", "-shared", "-fPIC", "-I", build.CSRC, src, "-o", so],
+                   check=True)
+    out = ctypes.CDLL(so)
+    f, d, i, ll = ctypes.c_float, ctypes.c_double, ctypes.c_int, ctypes.c_longlong
+    p = np.ctypeslib.ndpointer(np.float32, flags="C_CONTIGUOUS")
+    for name, res, args in (("score_bound", f, [p, p, i, i]), ("self_bound", d, [p, p, p, p, i, i, d]),
+                            ("cross_bound", d, [p, p, i, d]), ("bounded", i, [f, d, ll])):
+        getattr(out, name).restype, getattr(out, name).argtypes = res, args
+    return out

@@ -81,3 +81,46 @@ def test_uneven_gains_with_rotation():
     t["gq"][0::2], t["gq"][1::2] = 4.0, 0.25
     t["gk"][0::2], t["gk"][1::2] = 0.25, 4.0
     _run(w, blob)
+
+
+def _lean(w, sign, suffix=""):
+    """Biases that turn every query (and, times sign, every key) towards one direction, so all scores lie near the
+    bound of their gains times sign."""
+    s = np.where(np.arange(w["bq"].size) % 3 == 0, -1.0, 1.0)
+    w["bq" + suffix][:] = s
+    w["bk" + suffix][:] = sign * s
+
+
+class _Scores:
+    """Records the range of the oracle's scores in log2 units."""
+
+    def __init__(self, monkeypatch):
+        from oracle import xcache_oracle as xo
+        self.lo, self.hi = math.inf, -math.inf
+        attend = xo.softmax_attention
+
+        def record(q, k, v):
+            s = (q @ k.T) * (math.log2(math.e) / math.sqrt(q.shape[1]))
+            self.lo, self.hi = min(self.lo, s.min()), max(self.hi, s.max())
+            return attend(q, k, v)
+
+        monkeypatch.setattr(xo, "softmax_attention", record)
+
+
+@pytest.mark.parametrize("cross", [False, True])
+@pytest.mark.parametrize("head_dim", [64, 128])
+@pytest.mark.parametrize("sign", [1, -1])
+def test_value_range(sign, head_dim, cross, monkeypatch):
+    """All scores near 50 with values of 2^105, or near -50 with values of 2^-105: the products leave the range of a float
+    unless the row's maximum is subtracted, which the bound on the values decides."""
+    w = _workload(150, head_dim, cond_len=70 if cross else 0)
+    g = 1.9 if head_dim == 128 else 2.25
+    blob = _weights(w.model, 1.0 if cross else g, g)
+    t = synth.split_block_weights(w.model, blob, 0)
+    s = "_c" if cross else ""
+    _lean(t, sign if cross else -sign, s)  # (the gains of k have the other sign)
+    for name, scale in (("wv", 2.0 ** (105 * sign)), ("bv", 2.0 ** (105 * sign)), ("wo", 2.0 ** (-105 * sign))):
+        t[name + s] *= scale
+    sc = _Scores(monkeypatch)
+    _run(w, blob)
+    assert 40 < (sc.hi if sign > 0 else -sc.lo) < 64

@@ -1,0 +1,74 @@
+"""The rules that choose kernels, on the CPU."""
+import math
+
+import numpy as np
+import pytest
+
+import rules
+import synth
+from oracle import xcache_oracle as xo
+
+UNIT = math.log2(math.e)  # of a score bound per sqrt(d), besides its 2%
+
+
+def _bound(gq, gk, rope=0):
+    gq, gk = (np.asarray(g, np.float32) for g in (gq, gk))
+    return rules.lib().score_bound(gq, gk, len(gq), rope)
+
+
+@pytest.mark.parametrize("d", [64, 128])
+def test_score_bound_of_the_gains(d):
+    one = 1.02 * math.sqrt(d) * UNIT
+    assert _bound(np.full(d, 1.5), np.full(d, -2.0)) == pytest.approx(3 * one, rel=1e-6)
+    # products of 1 in every dimension, but a rotation mixes the two of a pair
+    gq, gk = np.tile([4.0, 0.25], d // 2), np.tile([0.25, 4.0], d // 2)
+    assert _bound(gq, gk) == pytest.approx(one, rel=1e-6)
+    assert _bound(gq, gk, rope=1) == pytest.approx(16 * one, rel=1e-6)
+    # one dimension, one pair
+    gq, gk = np.ones(d), np.ones(d)
+    gq[d - 1], gk[d - 2] = 3.0, 5.0
+    assert _bound(gq, gk) == pytest.approx(5 * one, rel=1e-6)
+    assert _bound(gq, gk, rope=1) == pytest.approx(15 * one, rel=1e-6)
+    for bad in (math.inf, -math.inf, math.nan):
+        gq[d // 2] = bad
+        for g in ((gq, gk), (gk, gq)):
+            for rope in (0, 1):
+                assert _bound(*g, rope) == math.inf
+    assert _bound(np.full(d, 1e30), np.full(d, 1e30)) == math.inf
+
+
+def test_bounded_attention_rule():
+    b = rules.lib().bounded
+    assert b(64.0, 1.0, 1) and not b(np.nextafter(np.float32(64), np.float32(65)), 1.0, 1)
+    # score + log2(keys) + log2(values) up to 120
+    assert b(50.0, 2.0 ** 50, 1 << 20) and not b(50.0, 2.0 ** 50.01, 1 << 20) and not b(50.0, 2.0 ** 50, (1 << 20) + 9999)
+    assert b(16.6, 2.0 ** 79, 1 << 24)
+    # score - log2(values) up to 92
+    assert b(50.0, 2.0 ** -42, 64) and not b(50.0, 2.0 ** -42.01, 64) and not b(16.6, 0.0, 64)
+    for bad in (math.inf, math.nan):
+        assert not b(bad, 1.0, 64) and not b(16.6, bad, 64)
+
+
+@pytest.mark.parametrize("action", [0.5, 40.0])
+def test_value_bounds_hold(action):
+    """Against the largest value that the oracle's block and cross-attention store; within a factor of 200 of it."""
+    m = synth.ModelShape(1, 256, 2, 128, 256, 64, 8, synth.BF16, 1, 1, (synth.ViewGroup(1, 1, 6, 7),), cond_len=20)
+    blob = synth.make_weights(m)
+    w = synth.split_block_weights(m, blob, 0)
+    w["b_ada"] += 0.5
+    w["bv"] -= 3.0
+    orc = xo.XCacheOracle(m, synth.GateParams(), blob)
+    cond = synth.condition_tokens(m)
+    orc.set_condition(cond)
+    a = np.full(8, action, np.float32)
+    x = next(iter(synth.latent_stream(m, synth.StreamParams(1, 0.9, 0.02), 0, 1))).astype(np.float64)
+    x[0] = 1e4 * np.eye(256)[3]  # a LayerNorm output of sqrt(C) in one column
+    _, (_, v) = orc.block(0, x, orc.cond(500.0, a), None)
+    c = np.ascontiguousarray
+    bound = rules.lib().self_bound(c(w["w_ada"]), c(w["b_ada"]), c(w["wv"]), c(w["bv"]), 256, m.cond_dim, max(1.0, action))
+    assert np.abs(v).max() <= bound <= 200 * np.abs(v).max()
+    bound = rules.lib().cross_bound(c(w["wv_c"]), c(w["bv_c"]), 256, float(np.abs(cond).max()))
+    assert np.abs(orc.cross_kv[0][1]).max() <= bound <= 200 * np.abs(orc.cross_kv[0][1]).max()
+    w["wv"][5, 7] = math.nan
+    assert not rules.lib().bounded(16.6, rules.lib().self_bound(c(w["w_ada"]), c(w["b_ada"]), c(w["wv"]), c(w["bv"]), 256,
+                                                               m.cond_dim, 1.0), 64)
