@@ -493,10 +493,10 @@ void cross_attention(xc_handle* h, int b, const int* flag, const PassWs& ws) {
       e.D = D;
       e.Mpad = (int)h->Mpad;
       e.Lcap = (int)h->Lcap_c;
-      launch_gemm(h->dtype, EPI_QKV, h->hbuf, wq_c, L, C, C, e, flag, h->st);
+      XC_HIP(launch_gemm(h->dtype, EPI_QKV, h->hbuf, wq_c, L, C, C, e, flag, h->st));
     } else {
       e.out_f32 = h->qkv;
-      launch_gemm(h->dtype, EPI_BIAS_F32, h->hbuf, wq_c, L, C, C, e, flag, h->st);
+      XC_HIP(launch_gemm(h->dtype, EPI_BIAS_F32, h->hbuf, wq_c, L, C, C, e, flag, h->st));
       launch_qk_norm(h->dtype, h->qkv, nullptr, nullptr, C, h->gq_c + (size_t)b * D, h->gk_c + (size_t)b * D,
                      RopeArgs{}, h->q, nullptr, nullptr, L, H, D, (int)h->Mpad, 0, 0, flag, h->st);
     }
@@ -517,7 +517,7 @@ void cross_attention(xc_handle* h, int b, const int* flag, const PassWs& ws) {
     e.out_f32 = h->x1;
     e.resid = h->x1;  // each element is read and then written by the same lane
     e.gate = h->ones;
-    launch_gemm(h->dtype, EPI_OPROJ, h->o, wptr<void>(h->wo_c, (size_t)b * C * C, esz), L, C, C, e, flag, h->st);
+    XC_HIP(launch_gemm(h->dtype, EPI_OPROJ, h->o, wptr<void>(h->wo_c, (size_t)b * C * C, esz), L, C, C, e, flag, h->st));
   }
 }
 
@@ -564,8 +564,8 @@ void compute_block(xc_handle* h, int b, const float* x, float* out, const int* f
     e.Lcap = (int)h->Lcap;
     e.kv_off = (int)kv_off;
     e.rope = h->rope;
-    launch_gemm(h->dtype, EPI_QKV, h->hbuf, wptr<void>(h->wqkv, (size_t)b * 3 * C * C, esz), L, 3 * C, C, e, flag,
-                h->st);
+    XC_HIP(launch_gemm(h->dtype, EPI_QKV, h->hbuf, wptr<void>(h->wqkv, (size_t)b * 3 * C * C, esz), L, 3 * C, C, e, flag,
+                       h->st));
   } else {
     {
       Prof p(h, XC_KERN_GEMM_QKV);
@@ -574,8 +574,8 @@ void compute_block(xc_handle* h, int b, const float* x, float* out, const int* f
       e.N = 3 * C;
       e.bias = h->bqkv + (size_t)b * 3 * C;
       e.out_f32 = h->qkv;
-      launch_gemm(h->dtype, EPI_BIAS_F32, h->hbuf, wptr<void>(h->wqkv, (size_t)b * 3 * C * C, esz), L, 3 * C, C, e,
-                  flag, h->st);
+      XC_HIP(launch_gemm(h->dtype, EPI_BIAS_F32, h->hbuf, wptr<void>(h->wqkv, (size_t)b * 3 * C * C, esz), L, 3 * C, C, e,
+                         flag, h->st));
     }
     Prof p(h, XC_KERN_QK_NORM);
     launch_qk_norm(h->dtype, h->qkv, h->qkv + C, h->qkv + 2 * C, 3 * C, h->gq + (size_t)b * D,
@@ -597,7 +597,7 @@ void compute_block(xc_handle* h, int b, const float* x, float* out, const int* f
     e.out_f32 = h->x1;
     e.resid = x;
     e.gate = gate1;
-    launch_gemm(h->dtype, EPI_OPROJ, h->o, wptr<void>(h->wo, (size_t)b * C * C, esz), L, C, C, e, flag, h->st);
+    XC_HIP(launch_gemm(h->dtype, EPI_OPROJ, h->o, wptr<void>(h->wo, (size_t)b * C * C, esz), L, C, C, e, flag, h->st));
   }
   if (h->Mc > 0) cross_attention(h, b, flag, ws);
   {
@@ -611,7 +611,7 @@ void compute_block(xc_handle* h, int b, const float* x, float* out, const int* f
     e.N = Dm;
     e.bias = h->b1 + (size_t)b * Dm;
     e.out_t = h->u;
-    launch_gemm(h->dtype, EPI_UP, h->hbuf, wptr<void>(h->w1, (size_t)b * Dm * C, esz), L, Dm, C, e, flag, h->st);
+    XC_HIP(launch_gemm(h->dtype, EPI_UP, h->hbuf, wptr<void>(h->w1, (size_t)b * Dm * C, esz), L, Dm, C, e, flag, h->st));
   }
   {
     Prof p(h, XC_KERN_GEMM_DOWN);
@@ -629,7 +629,7 @@ void compute_block(xc_handle* h, int b, const float* x, float* out, const int* f
       e.rb_split = h->rb_split;
       e.n_rb = h->n_rb;
     }
-    launch_gemm(h->dtype, EPI_DOWN, h->u, wptr<void>(h->w2, (size_t)b * C * Dm, esz), L, C, Dm, e, flag, h->st);
+    XC_HIP(launch_gemm(h->dtype, EPI_DOWN, h->u, wptr<void>(h->w2, (size_t)b * C * Dm, esz), L, C, Dm, e, flag, h->st));
   }
 }
 
@@ -1242,10 +1242,10 @@ xc_status xc_set_condition(xc_handle* h, const float* cond_host, int32_t n_token
         e.D = D;
         e.Mpad = (int)h->Mcpad;
         e.Lcap = (int)h->Lcap_c;
-        launch_gemm(h->dtype, EPI_QKV, h->cond_act, wkv, n_tokens, 2 * C, C, e, nullptr, h->st);
+        XC_HIP(launch_gemm(h->dtype, EPI_QKV, h->cond_act, wkv, n_tokens, 2 * C, C, e, nullptr, h->st));
       } else {
         e.out_f32 = h->cond_kv;
-        launch_gemm(h->dtype, EPI_BIAS_F32, h->cond_act, wkv, n_tokens, 2 * C, C, e, nullptr, h->st);
+        XC_HIP(launch_gemm(h->dtype, EPI_BIAS_F32, h->cond_act, wkv, n_tokens, 2 * C, C, e, nullptr, h->st));
         launch_qk_norm(h->dtype, nullptr, h->cond_kv, h->cond_kv + C, 2 * C, h->gq_c + (size_t)b * D,
                        h->gk_c + (size_t)b * D, RopeArgs{}, nullptr, kc_b, vt_b, n_tokens, H, D, 0,
                        (int)h->Lcap_c, 0, nullptr, h->st);

@@ -152,9 +152,7 @@ __device__ __forceinline__ void tile_epilogue(const EpiArgs& e, const f32x16 (&a
       for (int nt = 0; nt < NT; ++nt) {
         const float x = v[r][nt] + bias[nt];
         const int o = is + nt * 32;
-        if constexpr (MODE == EPI_BIAS_F32) {
-          __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, x), out_f, o * 4, 0, 0);
-        } else if constexpr (MODE == EPI_OPROJ) {
+        if constexpr (MODE == EPI_OPROJ) {
           const float y = res[slot][r][nt] + gate[nt] * x;
           __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, y), out_f, o * 4, 0, 0);
         } else if constexpr (MODE == EPI_UP) {
@@ -1019,11 +1017,6 @@ int cu_count() {
   return cus;
 }
 
-long long rounds_of(int M, int N, int BM, int BN, int slots) {
-  const long long tiles = (long long)((M + BM - 1) / BM) * (N / BN);
-  return (tiles + slots - 1) / slots;
-}
-
 // Tile of an M x N x K product.  Times are estimated in microseconds as rounds
 // * (fixed + K / 64 * stage), the constants fitted to launches of every tile at
 // 300 to 12096 rows, N and K 256 to 8192 (output and MLP products; fixed holds
@@ -1085,26 +1078,24 @@ void launch_wide(const void* A, const void* W, int M, int N, int K, const EpiArg
 }
 
 template <int MODE>
-void launch_mode(int dtype, const void* A, const void* W, int M, int N, int K, const EpiArgs& e, const int* flag,
-                 hipStream_t st) {
-  if constexpr (MODE != EPI_BIAS_F32) {
-    if (dtype == 1) {
-      constexpr bool qkv = MODE == EPI_QKV;
-      switch (pick_tile(M, N, K, qkv ? e.H * e.D : 0)) {
-        case kT64x64:
-          if constexpr (!qkv) launch_small_tile<MODE, 1, 1, 8, 2>(A, W, M, N, K, e, flag, st);
-          break;
-        case kT64x128: launch_small_tile<MODE, 1, 2, 3, 1>(A, W, M, N, K, e, flag, st); break;
-        case kT128x128deep: launch_small_tile<MODE, 2, 2, 5, 1>(A, W, M, N, K, e, flag, st); break;
-        case kT128x128: launch_small_tile<MODE, 2, 2, 2, 1>(A, W, M, N, K, e, flag, st); break;
-        case kT192x128deep: launch_small_tile<MODE, 3, 2, 4, 1>(A, W, M, N, K, e, flag, st); break;
-        case kT192x128: launch_small_tile<MODE, 3, 2, 2, 1>(A, W, M, N, K, e, flag, st); break;
-        case kT256x256: launch_wide<MODE, 256, true>(A, W, M, N, K, e, flag, st); break;
-        case kT192x256: launch_wide<MODE, 192, false>(A, W, M, N, K, e, flag, st); break;
-      }
-      return;
-    }
+void launch_bf16(const void* A, const void* W, int M, int N, int K, const EpiArgs& e, const int* flag, hipStream_t st) {
+  constexpr bool qkv = MODE == EPI_QKV;
+  switch (pick_tile(M, N, K, qkv ? e.H * e.D : 0)) {
+    case kT64x64:
+      if constexpr (!qkv) launch_small_tile<MODE, 1, 1, 8, 2>(A, W, M, N, K, e, flag, st);
+      break;
+    case kT64x128: launch_small_tile<MODE, 1, 2, 3, 1>(A, W, M, N, K, e, flag, st); break;
+    case kT128x128deep: launch_small_tile<MODE, 2, 2, 5, 1>(A, W, M, N, K, e, flag, st); break;
+    case kT128x128: launch_small_tile<MODE, 2, 2, 2, 1>(A, W, M, N, K, e, flag, st); break;
+    case kT192x128deep: launch_small_tile<MODE, 3, 2, 4, 1>(A, W, M, N, K, e, flag, st); break;
+    case kT192x128: launch_small_tile<MODE, 3, 2, 2, 1>(A, W, M, N, K, e, flag, st); break;
+    case kT256x256: launch_wide<MODE, 256, true>(A, W, M, N, K, e, flag, st); break;
+    case kT192x256: launch_wide<MODE, 192, false>(A, W, M, N, K, e, flag, st); break;
   }
+}
+
+template <int MODE>
+void launch_f32(const void* A, const void* W, int M, int N, int K, const EpiArgs& e, const int* flag, hipStream_t st) {
   // 16-byte rows; the operands are re-read by every tile, so the tiles grow
   // with the product, up to the staged 64 x 64 ones
   const long long t16 = (long long)((M + 15) / 16) * ((N + 15) / 16);
@@ -1126,17 +1117,35 @@ void launch_mode(int dtype, const void* A, const void* W, int M, int N, int K, c
 }  // namespace
 
 // bf16 requirements (checked by the caller): N % 128 == 0, K % 128 == 0, A has
-// at least roundup(M, 256) rows allocated; EPI_QKV needs C % 128 == 0 and
-// D in {64, 128}.
-void launch_gemm(int dtype, EpiMode mode, const void* A, const void* W, int M, int N, int K, const EpiArgs& e,
-                 const int* flag, hipStream_t st) {
+// at least roundup(M, 256) + 256 rows allocated; EPI_QKV needs C % 128 == 0 and
+// D in {64, 128}.  The plain EPI_BIAS_F32 product exists for float32 operands
+// only, EPI_QKV for bf16 ones only: anything else is refused.
+hipError_t launch_gemm(int dtype, EpiMode mode, const void* A, const void* W, int M, int N, int K, const EpiArgs& e,
+                       const int* flag, hipStream_t st) {
+  const bool bf = dtype == 1;
   switch (mode) {
-    case EPI_BIAS_F32: launch_mode<EPI_BIAS_F32>(dtype, A, W, M, N, K, e, flag, st); break;
-    case EPI_OPROJ: launch_mode<EPI_OPROJ>(dtype, A, W, M, N, K, e, flag, st); break;
-    case EPI_UP: launch_mode<EPI_UP>(dtype, A, W, M, N, K, e, flag, st); break;
-    case EPI_DOWN: launch_mode<EPI_DOWN>(dtype, A, W, M, N, K, e, flag, st); break;
-    case EPI_QKV: launch_mode<EPI_QKV>(dtype, A, W, M, N, K, e, flag, st); break;
+    case EPI_BIAS_F32:
+      if (bf) return hipErrorInvalidValue;
+      launch_f32<EPI_BIAS_F32>(A, W, M, N, K, e, flag, st);
+      break;
+    case EPI_OPROJ:
+      if (bf) launch_bf16<EPI_OPROJ>(A, W, M, N, K, e, flag, st);
+      else launch_f32<EPI_OPROJ>(A, W, M, N, K, e, flag, st);
+      break;
+    case EPI_UP:
+      if (bf) launch_bf16<EPI_UP>(A, W, M, N, K, e, flag, st);
+      else launch_f32<EPI_UP>(A, W, M, N, K, e, flag, st);
+      break;
+    case EPI_DOWN:
+      if (bf) launch_bf16<EPI_DOWN>(A, W, M, N, K, e, flag, st);
+      else launch_f32<EPI_DOWN>(A, W, M, N, K, e, flag, st);
+      break;
+    case EPI_QKV:
+      if (!bf) return hipErrorInvalidValue;
+      launch_bf16<EPI_QKV>(A, W, M, N, K, e, flag, st);
+      break;
   }
+  return hipSuccess;
 }
 
 }  // namespace xc

@@ -150,8 +150,9 @@ void launch_adaln(int dtype, const void* w_ada, const float* b_ada, const float*
 // (the skip path) instead of returning at entry
 void launch_ln_mod(int dtype, const float* x, const float* shift, const float* scale, void* out, int L, int C,
                    const int* flag, hipStream_t st, const void* rhat = nullptr, float* skip_out = nullptr);
-void launch_gemm(int dtype, EpiMode mode, const void* A, const void* W, int M, int N, int K, const EpiArgs& e,
-                 const int* flag, hipStream_t st);
+// hipErrorInvalidValue where the type has no such product (see the definition)
+hipError_t launch_gemm(int dtype, EpiMode mode, const void* A, const void* W, int M, int N, int K, const EpiArgs& e,
+                       const int* flag, hipStream_t st);
 // float32 models: per-head RMSNorm * gain of q and k (with the rotary
 // embedding when rope.tab != null), q -> q [H][Mpad][D], k / v -> the caches
 // at row / column kv_off + m.  qs, ks, vs: column 0 of each part in a

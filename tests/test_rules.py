@@ -1,4 +1,5 @@
 """The rules that choose kernels, on the CPU."""
+import ctypes
 import math
 
 import numpy as np
@@ -72,3 +73,16 @@ def test_value_bounds_hold(action):
     w["wv"][5, 7] = math.nan
     assert not rules.lib().bounded(16.6, rules.lib().self_bound(c(w["w_ada"]), c(w["b_ada"]), c(w["wv"]), c(w["bv"]), 256,
                                                                m.cond_dim, 1.0), 64)
+
+
+def test_products_without_a_kernel_are_refused():
+    """(type, epilogue) pairs that no kernel serves: refused before anything is launched (no other kernel may read
+    operands of the wrong type)."""
+    from paper_2604_20289_amd import xcache as xcp
+    launch = xcp.load_library()._ZN2xc11launch_gemmEiNS_7EpiModeEPKvS2_iiiRKNS_7EpiArgsEPKiP12ihipStream_t
+    vp, i = ctypes.c_void_p, ctypes.c_int
+    launch.restype, launch.argtypes = i, [i, i, vp, vp, i, i, i, ctypes.c_char_p, vp, vp]
+    bias_f32, qkv = 0, 4
+    f32, bf16 = 0, 1
+    for dtype, mode in ((bf16, bias_f32), (f32, qkv)):
+        assert launch(dtype, mode, None, None, 64, 128, 128, bytes(1024), None, None) == 1  # hipErrorInvalidValue
