@@ -6,6 +6,7 @@
 // non-null and the block's skip flag is set, the kernel returns at entry
 // (wave-uniformly), so a skipped block costs one empty launch.
 #include "xc_internal.h"
+#include "xc_rules.h"
 
 #include <math.h>
 
@@ -149,7 +150,7 @@ __global__ __launch_bounds__(256) void adaln_kernel(const T* __restrict__ w, con
 // contiguous [rows][dc] matrix, and a wave takes kRows consecutive rows, i.e.
 // one contiguous span of kRows * cpr chunks, walked lane-linearly (every load
 // instruction reads 1 KB of consecutive bytes).  Each chunk's dot product with
-// its slice of SiLU(c) goes to LDS; lane r < 32 then sums row r's cpr
+// its slice of SiLU(c) goes to LDS; lane r < kRows then sums row r's cpr
 // partials in order (deterministic).
 template <typename T, int kRows>
 __global__ __launch_bounds__(256) void adaln_flat_kernel(const T* __restrict__ w, const float* __restrict__ b,
@@ -439,11 +440,7 @@ void launch_adaln(int dtype, const void* w_ada, const float* b_ada, const float*
   int total = rows_per_block * n_blocks;
   const int esz = dtype == 1 ? 2 : 4;
   if ((dc * esz) % 16 == 0 && block_stride_w == (long long)rows_per_block * dc) {
-    // 32 rows per wave stream best once every CU has its workgroups; with fewer
-    // rows (models of few or narrow blocks) 8 spread them over the chip, one
-    // batch of loads per wave (HIP events: 8 blocks of hidden 512 10.2 -> 8.4 us, 2
-    // of 1536 12.7 -> 10.0)
-    const int rows = total >= 128 * 1024 ? 32 : 8;
+    const int rows = adaln_wave_rows(total, dc * esz / 16);
     const int grid = (total + 4 * rows - 1) / (4 * rows);
     const size_t lds = (size_t)4 * rows * (dc * esz / 16) * sizeof(float);
 #define XC_ADALN(T, R) \

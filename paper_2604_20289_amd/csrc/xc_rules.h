@@ -83,4 +83,18 @@ inline bool attention_bounded(float score_bound, double value_bound, long long L
   return score_bound <= 64.0f && score_bound + std::log2((double)Lk) + values <= 120.0 && score_bound - values <= 92.0;
 }
 
+// Rows of W_ada per wave in adaln_flat_kernel, 8 or 32, for `rows` rows of
+// `chunks` 16-byte chunks.  32 amortise a wave's fixed work but need many rows
+// to fill the chip, and 32 lanes then sum rows that lie `chunks` words apart in
+// LDS: multiples of 8 meet in few banks, and long rows leave few workgroups a
+// CU.  HIP events, us with 8 / 32 rows per wave:
+//   33 chunks (272 bf16): 49152 rows 10.3 / 11.1, 61440 11.6 / 11.7, 73728 13.5 / 12.8, 98304 15.5 / 13.9
+//   18 chunks (72 float): 49152 rows 7.8 / 8.3, 61440 8.6 / 8.6, 98304 12.0 / 9.8, 368640 30.3 / 24.2
+//   147456 rows: 24 chunks 16.9 / 14.8, 30 19.6 / 16.9, 32 21.7 / 26.7, 40 20.1 / 21.2, 42 21.3 / 20.9,
+//     50 24.9 / 23.6, 56 26.4 / 29.2, 64 36.6 / 51.3, 128 65.9 / 103
+inline int adaln_wave_rows(long long rows, int chunks) {
+  const bool spread = chunks <= 24 || (chunks <= 50 && chunks % 8 != 0);
+  return rows >= 60 * 1024 && spread ? 32 : 8;
+}
+
 }  // namespace xc

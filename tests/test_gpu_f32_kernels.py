@@ -37,3 +37,17 @@ def test_f32_kernels(name, rope):
         print(f"[f32] {name} rope={rope}: worst {max(ls.worst.values()):.2e}", flush=True)
     finally:
         ls.close()
+
+
+@pytest.mark.parametrize("blocks", [39, 40])
+def test_adaln_rows_per_wave(blocks):
+    """60840 modulation rows (8 per wave) and 62400 (32 per wave), neither a whole number of workgroups."""
+    from lockstep import Lockstep
+    m = synth.ModelShape(blocks, 260, 5, 52, 64, 64, 8, synth.F32, 1, 1, (synth.ViewGroup(1, 1, 3, 3),))
+    w = synth.Workload(f"f32-adaln-{blocks}", m, synth.GateParams(), synth.StreamParams(1, 0.97, 0.02))
+    ls = Lockstep(w)
+    try:
+        ls.run(1, tol_abs=1e-4)
+        print(f"[f32] adaLN {6 * 260 * blocks} rows: worst {max(ls.worst.values()):.2e}", flush=True)
+    finally:
+        ls.close()

@@ -75,6 +75,17 @@ def test_value_bounds_hold(action):
                                                                m.cond_dim, 1.0), 64)
 
 
+def test_adaln_wave_rows():
+    """8 rows per wave wherever 32 measured slower, 32 where 8 did (rows, 16-byte chunks per row)."""
+    rows = rules.lib().wave_rows
+    for n, chunks in ((12288, 18), (49152, 18), (49152, 33), (55296, 50), (73728, 32), (73728, 48), (147456, 40),
+                      (147456, 56), (147456, 128), (368640, 64)):
+        assert rows(n, chunks) == 8, (n, chunks)
+    for n, chunks in ((73728, 9), (61440, 18), (122880, 18), (368640, 18), (147456, 24), (147456, 30), (73728, 33), (368640, 34),
+                      (98304, 50)):
+        assert rows(n, chunks) == 32, (n, chunks)
+
+
 def test_products_without_a_kernel_are_refused():
     """(type, epilogue) pairs that no kernel serves: refused before anything is launched (no other kernel may read
     operands of the wrong type)."""
