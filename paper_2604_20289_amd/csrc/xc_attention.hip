@@ -21,6 +21,7 @@
 // (no running maximum), attn_bf16_kernel otherwise.
 // fp32 path: one workgroup per (query, head), plain online softmax.
 #include "xc_internal.h"
+#include "xc_rules.h"
 
 #include <math.h>
 
@@ -840,28 +841,28 @@ void launch_merge(bf16* o, int L, int H, int n_qt, int n_split, const float* ws,
   else attn_merge_kernel<D, 16><<<grid, 256, 0, st>>>(o, L, H, n_qt, n_split, ws, flag);
 }
 
-// float32: one workgroup per (query, head), its 4 waves take 64-key chunks in
+// float32: one workgroup per (query, head), its NW waves take 64-key chunks in
 // turn with an online softmax each and merge at the end.  Bound by latency, so
 // a lane's row of K (QK: one key per lane) and of V^T (PV: one head dim per
 // lane) are read as 16-byte loads in flight together where VEC (D % 4 == 0);
 // the scalar form takes any D <= 128.  64 queries, 128 keys, 4 heads of 32:
 // 17.8 us with one wave and scalar loads, 5.8 so.
-template <bool VEC>
-__global__ __launch_bounds__(256) void attn_f32_kernel(const float* __restrict__ Q, const float* __restrict__ Kc,
+template <bool VEC, int NW>
+__global__ __launch_bounds__(64 * NW) void attn_f32_kernel(const float* __restrict__ Q, const float* __restrict__ Kc,
                                                        const float* __restrict__ Vt, float* __restrict__ O, int L,
                                                        int Mpad, int Lcap, int Lk, int H, int D, float scale,
                                                        const int* __restrict__ flag) {
   if (flag != nullptr && *flag) return;
   __shared__ __attribute__((aligned(16))) float sq[128];
-  __shared__ __attribute__((aligned(16))) float sp[4][64];
-  __shared__ float sm[4], sl[4], so[4][128];
+  __shared__ __attribute__((aligned(16))) float sp[NW][64];
+  __shared__ float sm[NW], sl[NW], so[NW][128];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, q = blockIdx.x, h = blockIdx.y;
-  for (int i = threadIdx.x; i < D; i += 256) sq[i] = Q[((long long)h * Mpad + q) * D + i];
+  for (int i = threadIdx.x; i < D; i += 64 * NW) sq[i] = Q[((long long)h * Mpad + q) * D + i];
   __syncthreads();
   const float* Kh = Kc + (long long)h * Lcap * D;
   const float* Vh = Vt + (long long)h * D * Lcap;
   float m = -INFINITY, l = 0.f, o0 = 0.f, o1 = 0.f;
-  for (int k0 = wave * 64; k0 < Lk; k0 += 256) {
+  for (int k0 = wave * 64; k0 < Lk; k0 += 64 * NW) {
     const int key = k0 + lane;
     float s = -INFINITY;
     if (key < Lk) {
@@ -922,18 +923,19 @@ __global__ __launch_bounds__(256) void attn_f32_kernel(const float* __restrict__
   so[wave][lane + 64] = o1;
   __syncthreads();
   // waves that saw no key have m = -inf and weight 0 (wave 0 always saw one)
-  const float M = fmaxf(fmaxf(sm[0], sm[1]), fmaxf(sm[2], sm[3]));
-  float w[4], den = 0.f;
+  float M = sm[0], w[NW], den = 0.f;
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
+  for (int i = 1; i < NW; ++i) M = fmaxf(M, sm[i]);
+#pragma unroll
+  for (int i = 0; i < NW; ++i) {
     w[i] = i * 64 < Lk ? expf(sm[i] - M) : 0.f;
     den += w[i] * sl[i];
   }
   float* orow = O + (long long)q * H * D + h * D;
-  for (int d = threadIdx.x; d < D; d += 256) {
+  for (int d = threadIdx.x; d < D; d += 64 * NW) {
     float o = 0.f;
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+    for (int i = 0; i < NW; ++i)
       if (i * 64 < Lk) o += w[i] * so[i][d];
     orow[d] = o / den;
   }
@@ -1028,13 +1030,21 @@ void launch_attention(int dtype, const void* q, const void* kc, const void* vt, 
   } else {
     dim3 grid(L, H);
     const float scale = 1.0f / sqrtf((float)D);
+#define XC_ATTN_F32(VEC, NW)                                                                                  \
+  attn_f32_kernel<VEC, NW><<<grid, 64 * NW, 0, st>>>((const float*)q, (const float*)kc, (const float*)vt,      \
+                                                     (float*)o, L, Mpad, Lcap, Lk, H, D, scale, flag)
     // Lcap is a multiple of 64: with D % 4 == 0 every row of either cache is 16-byte aligned
-    if (D % 4 == 0)
-      attn_f32_kernel<true><<<grid, 256, 0, st>>>((const float*)q, (const float*)kc, (const float*)vt, (float*)o, L,
-                                                  Mpad, Lcap, Lk, H, D, scale, flag);
-    else
-      attn_f32_kernel<false><<<grid, 256, 0, st>>>((const float*)q, (const float*)kc, (const float*)vt, (float*)o, L,
-                                                   Mpad, Lcap, Lk, H, D, scale, flag);
+    const int waves = attention_f32_waves(Lk);
+    if (D % 4 == 0) {
+      if (waves == 1) XC_ATTN_F32(true, 1);
+      else if (waves == 2) XC_ATTN_F32(true, 2);
+      else XC_ATTN_F32(true, 4);
+    } else {
+      if (waves == 1) XC_ATTN_F32(false, 1);
+      else if (waves == 2) XC_ATTN_F32(false, 2);
+      else XC_ATTN_F32(false, 4);
+    }
+#undef XC_ATTN_F32
   }
 }
 

@@ -83,6 +83,12 @@ inline bool attention_bounded(float score_bound, double value_bound, long long L
   return score_bound <= 64.0f && score_bound + std::log2((double)Lk) + values <= 120.0 && score_bound - values <= 92.0;
 }
 
+// Waves of a float32 attention workgroup (one query of one head): no more than
+// the keys have 64-key chunks, the others would only cost the launch (3000
+// queries, 8 heads of 32, 20 keys: four waves 54.2 us, one 27.1; 4096 queries, 2
+// heads of 32, 65 keys: four 28.9, two 26.6; 200 queries, 800 keys: one 104, four 33).
+inline int attention_f32_waves(long long Lk) { return Lk <= 64 ? 1 : Lk <= 128 ? 2 : 4; }
+
 // Rows of W_ada per wave in adaln_flat_kernel, 8 or 32, for `rows` rows of
 // `chunks` 16-byte chunks.  32 amortise a wave's fixed work but need many rows
 // to fill the chip, and 32 lanes then sum rows that lie `chunks` words apart in

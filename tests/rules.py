@@ -27,6 +27,7 @@ double cross_bound(const float* wv, const float* bv, int C, double cond_max) {
   return cross_value_bound(v, C, cond_max);
 }
 int wave_rows(long long rows, int chunks) { return adaln_wave_rows(rows, chunks); }
+int f32_waves(long long Lk) { return attention_f32_waves(Lk); }
 int bounded(float score, double value, long long Lk) { return attention_bounded(score, value, Lk); }
 }
 """
@@ -44,6 +45,7 @@ def lib():
     f, d, i, ll = ctypes.c_float, ctypes.c_double, ctypes.c_int, ctypes.c_longlong
     p = np.ctypeslib.ndpointer(np.float32, flags="C_CONTIGUOUS")
     for name, res, args in (("score_bound", f, [p, p, i, i]), ("self_bound", d, [p, p, p, p, i, i, d]),
-                            ("cross_bound", d, [p, p, i, d]), ("bounded", i, [f, d, ll]), ("wave_rows", i, [ll, i])):
+                            ("cross_bound", d, [p, p, i, d]), ("bounded", i, [f, d, ll]), ("wave_rows", i, [ll, i]),
+                            ("f32_waves", i, [ll])):
         getattr(out, name).restype, getattr(out, name).argtypes = res, args
     return out

@@ -51,3 +51,23 @@ def test_adaln_rows_per_wave(blocks):
         print(f"[f32] adaLN {6 * 260 * blocks} rows: worst {max(ls.worst.values()):.2e}", flush=True)
     finally:
         ls.close()
+
+
+@pytest.mark.parametrize("cond", [1, 63, 64, 65, 128, 129, 257])
+@pytest.mark.parametrize("head_dim", [6, 64, 128])
+def test_attention_waves(head_dim, cond):
+    """Cross-attention with one, two and four waves per query at the edges of their chunks, scalar and 16-byte rows."""
+    from lockstep import Lockstep
+    m = synth.ModelShape(1, 2 * head_dim, 2, head_dim, 64, 64, 8, synth.F32, 1, 1, (synth.ViewGroup(1, 1, 3, 7),),
+                         cond_len=cond)
+    w = synth.Workload(f"f32-waves-d{head_dim}-c{cond}", m, synth.GateParams(), synth.StreamParams(1, 0.97, 0.02))
+    blob = synth.make_weights(m)
+    t = synth.split_block_weights(m, blob, 0)
+    t["wv_c"] *= 8
+    t["wo_c"] *= 8
+    ls = Lockstep(w, weights=blob)
+    try:
+        ls.run(1, tol_abs=1e-4)
+        print(f"[f32] d={head_dim} {cond} keys: worst {max(ls.worst.values()):.2e}", flush=True)
+    finally:
+        ls.close()

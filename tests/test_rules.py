@@ -86,6 +86,10 @@ def test_adaln_wave_rows():
         assert rows(n, chunks) == 32, (n, chunks)
 
 
+def test_f32_attention_waves():
+    assert [rules.lib().f32_waves(k) for k in (1, 64, 65, 128, 129, 1 << 24)] == [1, 1, 2, 2, 4, 4]
+
+
 def test_products_without_a_kernel_are_refused():
     """(type, epilogue) pairs that no kernel serves: refused before anything is launched (no other kernel may read
     operands of the wrong type)."""
