@@ -846,16 +846,19 @@ void launch_merge(bf16* o, int L, int H, int n_qt, int n_split, const float* ws,
 // a lane's row of K (QK: one key per lane) and of V^T (PV: one head dim per
 // lane) are read as 16-byte loads in flight together where VEC (D % 4 == 0);
 // the scalar form takes any D <= 128.  64 queries, 128 keys, 4 heads of 32:
-// 17.8 us with one wave and scalar loads, 5.8 so.
+// 17.8 us with one wave and scalar loads, 5.8 so.  One wave alone (at most 64
+// keys) has many queries to serve and little to do for each: it keeps to 64
+// registers (eight waves a SIMD), loads rows by four chunks whatever their
+// number and merges nothing.  2000 queries, 16 heads of 16: 1 / 7 / 64 keys 22.3 /
+// 25.5 / 40.9 us without these, 17.3 / 18.4 / 41.2 with (16.2 / 21.3 / 80 in scalar loads).
 template <bool VEC, int NW>
-__global__ __launch_bounds__(64 * NW) void attn_f32_kernel(const float* __restrict__ Q, const float* __restrict__ Kc,
+__global__ __launch_bounds__(64 * NW, NW == 1 ? 8 : 4) void attn_f32_kernel(const float* __restrict__ Q, const float* __restrict__ Kc,
                                                        const float* __restrict__ Vt, float* __restrict__ O, int L,
                                                        int Mpad, int Lcap, int Lk, int H, int D, float scale,
                                                        const int* __restrict__ flag) {
   if (flag != nullptr && *flag) return;
   __shared__ __attribute__((aligned(16))) float sq[128];
   __shared__ __attribute__((aligned(16))) float sp[NW][64];
-  __shared__ float sm[NW], sl[NW], so[NW][128];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, q = blockIdx.x, h = blockIdx.y;
   for (int i = threadIdx.x; i < D; i += 64 * NW) sq[i] = Q[((long long)h * Mpad + q) * D + i];
   __syncthreads();
@@ -869,10 +872,23 @@ __global__ __launch_bounds__(64 * NW) void attn_f32_kernel(const float* __restri
       float acc = 0.f;
       if constexpr (VEC) {
         const float4* kr = reinterpret_cast<const float4*>(Kh + (long long)key * D);
-#pragma unroll 8
-        for (int i = 0; i < D / 4; ++i) {
-          const float4 kv = kr[i], qv = reinterpret_cast<const float4*>(sq)[i];
+        const float4* qr = reinterpret_cast<const float4*>(sq);
+        const int n4 = D / 4;
+        auto dot = [&](float4 qv, float4 kv) __attribute__((always_inline)) {
           acc += qv.x * kv.x + qv.y * kv.y + qv.z * kv.z + qv.w * kv.w;
+        };
+        if constexpr (NW == 1) {
+          for (int i = 0; i < n4; i += 4) {  // past the row: its last chunk, not added
+            float4 kv[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) kv[u] = kr[min(i + u, n4 - 1)];
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+              if (i + u < n4) dot(qr[i + u], kv[u]);
+          }
+        } else {
+#pragma unroll 8
+          for (int i = 0; i < n4; ++i) dot(qr[i], kr[i]);
         }
       } else {
         for (int i = 0; i < D; ++i) acc += sq[i] * Kh[(long long)key * D + i];
@@ -899,11 +915,21 @@ __global__ __launch_bounds__(64 * NW) void attn_f32_kernel(const float* __restri
       const float* vr = Vh + (long long)d * Lcap + k0;
       int jj = 0;
       if constexpr (VEC) {
-#pragma unroll 4
-        for (; jj + 4 <= nk; jj += 4) {
+        // rows of V^T are whole 64-key chunks: one wave's last keys in one load too
+        const int n4 = nk & ~3;
+        float4 last = {};
+        if constexpr (NW == 1) last = *reinterpret_cast<const float4*>(vr + min(n4, 60));
+#pragma unroll (NW == 1 ? 2 : 4)
+        for (; jj < n4; jj += 4) {
           const float4 vv = *reinterpret_cast<const float4*>(vr + jj);
           const float4 pp = *reinterpret_cast<const float4*>(&sp[wave][jj]);
           o += pp.x * vv.x + pp.y * vv.y + pp.z * vv.z + pp.w * vv.w;
+        }
+        if constexpr (NW == 1) {
+          if (jj < nk) o += sp[wave][jj] * last.x;
+          if (jj + 1 < nk) o += sp[wave][jj + 1] * last.y;
+          if (jj + 2 < nk) o += sp[wave][jj + 2] * last.z;
+          return o;
         }
       }
       for (; jj < nk; ++jj) o += sp[wave][jj] * vr[jj];
@@ -915,29 +941,35 @@ __global__ __launch_bounds__(64 * NW) void attn_f32_kernel(const float* __restri
     __builtin_amdgcn_wave_barrier();
     m = m_new;
   }
-  if (lane == 0) {
-    sm[wave] = m;
-    sl[wave] = l;
-  }
-  so[wave][lane] = o0;
-  so[wave][lane + 64] = o1;
-  __syncthreads();
-  // waves that saw no key have m = -inf and weight 0 (wave 0 always saw one)
-  float M = sm[0], w[NW], den = 0.f;
-#pragma unroll
-  for (int i = 1; i < NW; ++i) M = fmaxf(M, sm[i]);
-#pragma unroll
-  for (int i = 0; i < NW; ++i) {
-    w[i] = i * 64 < Lk ? expf(sm[i] - M) : 0.f;
-    den += w[i] * sl[i];
-  }
   float* orow = O + (long long)q * H * D + h * D;
-  for (int d = threadIdx.x; d < D; d += 64 * NW) {
-    float o = 0.f;
+  if constexpr (NW == 1) {  // nothing to merge
+    if (lane < D) orow[lane] = o0 / l;
+    if (lane + 64 < D) orow[lane + 64] = o1 / l;
+  } else {
+    __shared__ float sm[NW], sl[NW], so[NW][128];
+    if (lane == 0) {
+      sm[wave] = m;
+      sl[wave] = l;
+    }
+    so[wave][lane] = o0;
+    so[wave][lane + 64] = o1;
+    __syncthreads();
+    // waves that saw no key have m = -inf and weight 0 (wave 0 always saw one)
+    float M = sm[0], w[NW], den = 0.f;
 #pragma unroll
-    for (int i = 0; i < NW; ++i)
-      if (i * 64 < Lk) o += w[i] * so[i][d];
-    orow[d] = o / den;
+    for (int i = 1; i < NW; ++i) M = fmaxf(M, sm[i]);
+#pragma unroll
+    for (int i = 0; i < NW; ++i) {
+      w[i] = i * 64 < Lk ? expf(sm[i] - M) : 0.f;
+      den += w[i] * sl[i];
+    }
+    for (int d = threadIdx.x; d < D; d += 64 * NW) {
+      float o = 0.f;
+#pragma unroll
+      for (int i = 0; i < NW; ++i)
+        if (i * 64 < Lk) o += w[i] * so[i][d];
+      orow[d] = o / den;
+    }
   }
 }
 

@@ -53,10 +53,15 @@ def test_adaln_rows_per_wave(blocks):
         ls.close()
 
 
-@pytest.mark.parametrize("cond", [1, 63, 64, 65, 128, 129, 257])
-@pytest.mark.parametrize("head_dim", [6, 64, 128])
+# one, two and four waves per query at the edges of their chunks, scalar and 16-byte rows; one wave's rows of 1, 5 and 17
+# sixteen-byte chunks (it loads four at a time) and 1 to 3 keys past a multiple of four
+WAVES = ([(d, c) for d in (6, 64, 128) for c in (1, 63, 64, 65, 128, 129, 257)]
+         + [(d, c) for d in (4, 20, 68) for c in (2, 3, 4, 61, 62)])
+
+
+@pytest.mark.parametrize("head_dim,cond", WAVES)
 def test_attention_waves(head_dim, cond):
-    """Cross-attention with one, two and four waves per query at the edges of their chunks, scalar and 16-byte rows."""
+    """Cross-attention to few keys."""
     from lockstep import Lockstep
     m = synth.ModelShape(1, 2 * head_dim, 2, head_dim, 64, 64, 8, synth.F32, 1, 1, (synth.ViewGroup(1, 1, 3, 7),),
                          cond_len=cond)
