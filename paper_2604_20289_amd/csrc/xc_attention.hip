@@ -1043,9 +1043,10 @@ void launch_attention(int dtype, const void* q, const void* kc, const void* vt, 
     const int n_split = attention_splits(L, Lk, H, D, ws != nullptr ? ws_floats : 0);
     const int units = H * n_split * n_qt;
     const int grid = (units + kXcds - 1) / kXcds * kXcds;
+    const bool wide = bounded && attention_wide_waves(L, Lk, D, (long long)H * n_qt, resident_attention_groups());
 #define XC_ATTN(DD)                                                                                                \
   do {                                                                                                             \
-    if (bounded)                                                                                                   \
+    if (wide)                                                                                                      \
       attn_bounded_kernel<DD><<<grid, 64 * kBWaves, 0, st>>>((const bf16*)q, (const bf16*)kc, (const bf16*)vt,     \
                                                              (bf16*)o, L, Mpad, Lcap, Lk, H, n_qt, n_split, ws,    \
                                                              flag);                                                \

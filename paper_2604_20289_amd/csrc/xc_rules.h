@@ -83,6 +83,26 @@ inline bool attention_bounded(float score_bound, double value_bound, long long L
   return score_bound <= 64.0f && score_bound + std::log2((double)Lk) + values <= 120.0 && score_bound - values <= 92.0;
 }
 
+// Whether the kernel without a running maximum (four waves of 64 queries) is the
+// faster one for L queries over Lk keys, `items` (head, 256-query) items on
+// `cus` CUs; otherwise the running-maximum kernel (eight waves of 32) serves
+// them.  Up to 128 queries leave half of the 64-query waves idle, and a wave's
+// tile is a longer chain; two key tiles are the running-maximum kernel's
+// shortest loop, unless two workgroups of 64 head dims share a CU.  us without
+// / with a running maximum:
+//   33 queries, 8 heads of 64: 128 keys 8.7 / 8.1, 448 keys 12.6 / 10.9, 1024 keys 12.4 / 11.9
+//   128 queries, 8 heads of 128: 64 keys 10.5 / 10.5, 128 keys 12.3 / 11.7, 1024 keys 16.9 / 15.9
+//   160 queries, 8 heads of 64: 64 keys 8.2 / 8.8, 192 keys 10.6 / 10.4, 448 keys 13.9 / 13.9
+//   9522 queries, 15 heads of 128: 64 keys 37.2 / 37.7, 128 keys 45.9 / 43.8, 192 keys 50.4 / 53.5, 256 keys
+//     54.5 / 53.1, 384 keys 63.7 / 62.6, 512 keys 72.4 / 72.2, 2048 keys 178 / 189
+//   3245 queries, 16 heads of 64 (208 items): 128 keys 12.4 / 11.9, 256 keys 14.2 / 13.9, 384 keys 16.2 / 16.1
+//   7020 queries, 16 heads of 64 (448 items): 128 keys 17.0 / 20.2, 256 keys 21.7 / 24.6
+inline bool attention_wide_waves(int L, long long Lk, int D, long long items, int cus) {
+  const long long tiles = (Lk + 63) / 64;
+  if (L <= 128) return false;
+  return tiles != 2 || (D == 64 && items > cus);
+}
+
 // Waves of a float32 attention workgroup (one query of one head): no more than
 // the keys have 64-key chunks, the others would only cost the launch (3000
 // queries, 8 heads of 32, 20 keys: four waves 54.2 us, one 27.1; 4096 queries, 2

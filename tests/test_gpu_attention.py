@@ -11,6 +11,7 @@ import math
 import numpy as np
 import pytest
 
+import rules
 import synth
 
 torch = pytest.importorskip("torch")
@@ -19,7 +20,8 @@ pytestmark = pytest.mark.gpu
 # tokens: with a window of 3 chunks the passes see 1 / 2 / 2, 2 / 4 / 5, 3 / 5 / 8
 # and 5 / 9 / 13 key tiles of 64
 TOKENS = {40: (1, 1, 2, 20), 100: (1, 2, 5, 10), 150: (1, 3, 5, 10), 257: (1, 1, 1, 257), 300: (2, 3, 5, 10)}
-# gains 1: |score| <= sqrt(128) log2(e) = 16.3; gains 2.5: 6.25 times that, past the bound of 64
+# gains 1: |score| <= sqrt(128) log2(e) = 16.3; gains 2.5: 6.25 times that, past the bound of 64 (up to 128 queries the
+# running maximum serves both)
 GAINS = {"bounded": 1.0, "running-max": 2.5}
 
 
@@ -81,6 +83,30 @@ def test_uneven_gains_with_rotation():
     t["gq"][0::2], t["gq"][1::2] = 4.0, 0.25
     t["gk"][0::2], t["gk"][1::2] = 0.25, 4.0
     _run(w, blob)
+
+
+@pytest.mark.parametrize("cond", [5, 64])
+@pytest.mark.parametrize("head_dim", [64, 128])
+def test_one_key_tile(head_dim, cond):
+    """Cross-attention without a running maximum over a single key tile, ragged and whole."""
+    w = _workload(150, head_dim, cond_len=cond)
+    _run(w, _weights(w.model, 1.0))
+
+
+@pytest.mark.parametrize("cond", [100, 128])
+def test_two_key_tiles_many_items(cond):
+    """Two key tiles, 17 query tiles in 16 heads of 64: more items than CUs, so no running maximum."""
+    m = synth.ModelShape(1, 1024, 16, 64, 128, 64, 8, synth.BF16, 1, 1, (synth.ViewGroup(1, 1, 1, 4100),), cond_len=cond)
+    w = synth.Workload(f"attention-h1024-d64-c{cond}", m, synth.GateParams(), synth.StreamParams(1, 0.97, 0.02))
+    assert rules.lib().wide_waves(4100, cond, 64, 16 * 17, torch.cuda.get_device_properties(0).multi_processor_count)
+    blob = _weights(m, 1.0)
+    from lockstep import Lockstep
+    ls = Lockstep(w, weights=blob, compute=np.float32)
+    try:
+        ls.run(1, tol_rel_l2=2e-2)
+        print(f"[attention] {w.name}: worst {max(ls.worst.values()):.2e}", flush=True)
+    finally:
+        ls.close()
 
 
 def _lean(w, sign, suffix=""):

@@ -50,6 +50,17 @@ def test_bounded_attention_rule():
         assert not b(bad, 1.0, 64) and not b(16.6, bad, 64)
 
 
+def test_attention_wide_waves():
+    """64-query waves wherever they measured faster (queries, keys, head dim, items on 256 CUs)."""
+    wide = rules.lib().wide_waves
+    for case in ((9522, 64, 128, 570), (9522, 129, 128, 570), (9522, 21060, 128, 570), (3510, 256, 128, 84), (160, 64, 64, 8),
+                 (7020, 128, 64, 448), (3245, 6490, 64, 208), (129, 129, 128, 2)):
+        assert wide(*case, 256), case
+    for case in ((33, 448, 64, 8), (128, 1024, 128, 8), (128, 128, 64, 512), (9522, 128, 128, 570), (9522, 65, 128, 570),
+                 (3245, 128, 64, 208), (3245, 65, 64, 256)):
+        assert not wide(*case, 256), case
+
+
 @pytest.mark.parametrize("action", [0.5, 40.0])
 def test_value_bounds_hold(action):
     """Against the largest value that the oracle's block and cross-attention store; within a factor of 200 of it."""
