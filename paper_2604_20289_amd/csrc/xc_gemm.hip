@@ -20,6 +20,7 @@
 // for products with few tiles, a plain LDS-tiled FMA GEMM (64x64 tiles, 4x4 per
 // thread) beyond.
 #include "xc_internal.h"
+#include "xc_rules.h"
 
 #include <math.h>
 
@@ -1017,50 +1018,6 @@ int cu_count() {
   return cus;
 }
 
-// Tile of an M x N x K product.  Times are estimated in microseconds as rounds
-// * (fixed + K / 64 * stage), the constants fitted to launches of every tile at
-// 300 to 12096 rows, N and K 256 to 8192 (output and MLP products; fixed holds
-// the launch, the first stage's latency and the epilogue).  Small tiles run one
-// workgroup per CU with a deep ring or two with a shallow one; a shallow 64 x
-// 128 tile with its CU to itself takes its own line.
-//   768 x 512 x 2048 (MLP down): 64 x 64 13.0 us, 64 x 128 15.4, 128 x 128 20.4
-//   3245 x 1024 x 4096: 64 x 128 44.1, 128 x 128 deep 38.9, 192 x 128 56.9
-//   3510 x 2304 x 768 (QKV): 64 x 128 30.6, 128 x 128 shallow 26.1
-//   7020 x 1536 x 6144: 128 x 128 172, 192 x 128 142, 192 x 256 133, 256 x 256 161
-//   12096 x 6144 x 2048 (QKV): 256 x 256 275 (5 rounds), 192 x 256 364 (6 rounds)
-//   12096 x 2048 x 8192: 192 x 128 381, 192 x 256 365, 256 x 256 408
-struct Tile {
-  int id, bm, bn, per_cu;
-  double fixed, stage;
-};
-enum TileId { kT64x64, kT64x128, kT128x128deep, kT128x128, kT192x128deep, kT192x128, kT256x256, kT192x256 };
-constexpr Tile kTiles[] = {
-    {kT64x64, 64, 64, 1, 6.5, 0.24},         {kT64x128, 64, 128, 1, 6.0, 0.31},
-    {kT64x128, 64, 128, 2, 7.5, 0.60},       {kT128x128deep, 128, 128, 1, 8.5, 0.48},
-    {kT128x128, 128, 128, 2, 9.5, 0.93},     {kT192x128deep, 192, 128, 1, 10.0, 0.65},
-    {kT192x128, 192, 128, 2, 13.5, 1.38},    {kT256x256, 256, 256, 1, 12.0, 1.50},
-    {kT192x256, 192, 256, 1, 14.0, 1.31},
-};
-
-// C: columns of each of q, k, v for the QKV epilogue (0: another epilogue)
-int pick_tile(int M, int N, int K, int C) {
-  const int cus = cu_count();
-  int best = kT64x128;
-  double best_us = 1e300;
-  for (const Tile& t : kTiles) {
-    if (N % t.bn != 0) continue;
-    // a QKV tile lies in one of q, k, v, its waves hold 64 columns
-    if (C != 0 && (C % t.bn != 0 || t.id == kT64x64)) continue;
-    const long long tiles = (long long)((M + t.bm - 1) / t.bm) * (N / t.bn), slots = (long long)cus * t.per_cu;
-    const double us = (double)((tiles + slots - 1) / slots) * (t.fixed + K / 64 * t.stage);
-    if (us < best_us) {
-      best_us = us;
-      best = t.id;
-    }
-  }
-  return best;
-}
-
 template <int MODE, int MT, int NT, int NS, int G>
 void launch_small_tile(const void* A, const void* W, int M, int N, int K, const EpiArgs& e, const int* flag,
                        hipStream_t st) {
@@ -1080,7 +1037,7 @@ void launch_wide(const void* A, const void* W, int M, int N, int K, const EpiArg
 template <int MODE>
 void launch_bf16(const void* A, const void* W, int M, int N, int K, const EpiArgs& e, const int* flag, hipStream_t st) {
   constexpr bool qkv = MODE == EPI_QKV;
-  switch (pick_tile(M, N, K, qkv ? e.H * e.D : 0)) {
+  switch (pick_tile(M, N, K, qkv ? e.H * e.D : 0, cu_count())) {
     case kT64x64:
       if constexpr (!qkv) launch_small_tile<MODE, 1, 1, 8, 2>(A, W, M, N, K, e, flag, st);
       break;

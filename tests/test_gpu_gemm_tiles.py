@@ -8,28 +8,35 @@ computes in float32 with bf16 storage rounding."""
 import numpy as np
 import pytest
 
+import rules
 import synth
 
 torch = pytest.importorskip("torch")
 pytestmark = pytest.mark.gpu
 
-# The tiles the launcher picks on 256 CUs (output / MLP up / MLP down; QKV):
-#   h384-L16000: 192 x 128 with a four-slot ring, K = 384 (six stages); the same
-#   h1152-L7020: 128 x 128 with two slots, K = 1152; 192 x 128 with two
-#   h768-L16000: 192 x 256, K = 768; the same
-#   h2048-L6100: 192 x 256, K = 2048 / 64 x 64 / 256 x 256, K = 128; 192 x 256
-#   h640-L5000: 128 x 128 with five slots, K = 640 and 1280, 128 x 128 with two; 192 x 128
-#   h1024-L1100: 128 x 128 with five slots, K = 1024, also in the QKV product
-#   h256-L70: 64 x 128 and 64 x 64, K = 256 (four stages) and 1024
+# name: (hidden, heads, mlp, grid, the tiles the launcher picks on 256 CUs for QKV, output, MLP up and MLP down).  "deep":
+# one workgroup per CU with a deep stage ring.  K = hidden, but mlp for MLP down
 SHAPES = {
-    "h384-L16000": (384, 3, 384, (1, 1, 125, 128)),
-    "h1152-L7020": (1152, 9, 1152, (2, 3, 26, 45)),
-    "h768-L16000": (768, 6, 768, (1, 1, 125, 128)),
-    "h2048-L6100": (2048, 16, 128, (1, 1, 61, 100)),
-    "h640-L5000": (640, 5, 1280, (2, 1, 50, 50)),
-    "h1024-L1100": (1024, 8, 1024, (1, 1, 44, 25)),
-    "h256-L70": (256, 2, 1024, (1, 1, 7, 10)),
+    "h384-L16000": (384, 3, 384, (1, 1, 125, 128), ("192x128 deep", "192x128 deep", "192x128 deep", "192x128 deep")),
+    "h1152-L7020": (1152, 9, 1152, (2, 3, 26, 45), ("192x128", "128x128", "128x128", "128x128")),
+    "h768-L16000": (768, 6, 768, (1, 1, 125, 128), ("192x256", "192x256", "192x256", "192x256")),
+    "h2048-L6100": (2048, 16, 128, (1, 1, 61, 100), ("192x256", "192x256", "64x64", "256x256")),
+    "h640-L5000": (640, 5, 1280, (2, 1, 50, 50), ("192x128", "128x128 deep", "128x128", "128x128 deep")),
+    "h1024-L1100": (1024, 8, 1024, (1, 1, 44, 25), ("128x128 deep", "64x128", "64x128", "64x128")),
+    "h256-L70": (256, 2, 1024, (1, 1, 7, 10), ("64x128", "64x128", "64x128", "64x64")),
+    "h640-L13477": (640, 5, 256, (1, 1, 1, 13477), ("128x128", "192x128", "128x128 deep", "192x128")),
+    "h640-mlp640-L13477": (640, 10, 640, (1, 1, 1, 13477), ("128x128", "192x128", "192x128", "192x128")),
+    "h256-L10982": (256, 4, 1024, (1, 2, 17, 323), ("256x256", "64x128", "256x256", "128x128 deep")),
+    "h1024-L12479": (1024, 8, 128, (1, 1, 1, 12479), ("256x256", "256x256", "64x128", "256x256")),
+    "h512-L16": (512, 4, 128, (1, 1, 4, 4), ("64x128", "64x64", "64x64", "64x128")),
 }
+
+
+def products(name):
+    """{epilogue: (M, N, K, columns of each of q, k, v)} of a shape's four products."""
+    C, _, Dm, g, _ = SHAPES[name]
+    L = g[0] * g[1] * g[2] * g[3]
+    return {"qkv": (L, 3 * C, C, C), "output": (L, C, C, 0), "up": (L, Dm, C, 0), "down": (L, C, Dm, 0)}
 
 
 @pytest.mark.parametrize("name", sorted(SHAPES))
@@ -38,7 +45,9 @@ def test_gemm_tiles(name):
     from lockstep import rel_l2
     from oracle import xcache_oracle as xo
     from paper_2604_20289_amd.xcache import XC_CACHE_KEYS, XC_CACHE_VALUES, XCache
-    C, H, Dm, grid = SHAPES[name]
+    C, H, Dm, grid, tiles = SHAPES[name]
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    assert [rules.tile(*p, cus) for p in products(name).values()] == list(tiles)
     m = synth.ModelShape(1, C, H, C // H, Dm, 256, 16, synth.BF16, 1, 1, (synth.ViewGroup(*grid),))
     gate = synth.GateParams(front_anchors=0)
     blob = synth.make_weights(m)

@@ -101,6 +101,20 @@ def test_f32_attention_waves():
     assert [rules.lib().f32_waves(k) for k in (1, 64, 65, 128, 129, 1 << 24)] == [1, 1, 2, 2, 4, 4]
 
 
+def test_gemm_tiles_are_all_tested():
+    """The tiles that the GPU test of the products names are the ones the rule picks, and every tile that an epilogue can
+    take is among them."""
+    import test_gpu_gemm_tiles as gt
+    seen = {}
+    for name, shape in gt.SHAPES.items():
+        picked = {e: rules.tile(*p, 256) for e, p in gt.products(name).items()}
+        assert tuple(picked.values()) == shape[4], name
+        for e, t in picked.items():
+            seen.setdefault(e, set()).add(t)
+    everything = set(rules.TILES)
+    assert seen == {"qkv": everything - {"64x64"}, "output": everything, "up": everything, "down": everything}
+
+
 def test_products_without_a_kernel_are_refused():
     """(type, epilogue) pairs that no kernel serves: refused before anything is launched (no other kernel may read
     operands of the wrong type)."""
