@@ -118,19 +118,70 @@ def _lean(w, sign, suffix=""):
 
 
 class _Scores:
-    """Records the range of the oracle's scores in log2 units."""
+    """Records the range of the oracle's scores in log2 units, and the lowest maximum of a row."""
 
     def __init__(self, monkeypatch):
         from oracle import xcache_oracle as xo
-        self.lo, self.hi = math.inf, -math.inf
+        self.lo, self.hi, self.row_max = math.inf, -math.inf, math.inf
         attend = xo.softmax_attention
 
         def record(q, k, v):
             s = (q @ k.T) * (math.log2(math.e) / math.sqrt(q.shape[1]))
             self.lo, self.hi = min(self.lo, s.min()), max(self.hi, s.max())
+            self.row_max = min(self.row_max, s.max(axis=1).min())
             return attend(q, k, v)
 
         monkeypatch.setattr(xo, "softmax_attention", record)
+
+
+def _lean_workload(head_dim, cross, gain, sign):
+    """One direction for every query and key of the self- or the cross-attention, with these gains."""
+    w = _workload(150, head_dim, cond_len=70 if cross else 0)
+    blob = _weights(w.model, 1.0 if cross else gain, gain)
+    s = "_c" if cross else ""
+    t = synth.split_block_weights(w.model, blob, 0)
+    _lean(t, sign if cross else -sign, s)  # (the gains of k have the other sign)
+    bound = rules.lib().score_bound(np.ascontiguousarray(t["gq" + s]), np.ascontiguousarray(t["gk" + s]), head_dim, 0)
+    return w, blob, t, s, bound
+
+
+@pytest.mark.parametrize("cross", [False, True])
+@pytest.mark.parametrize("head_dim", [64, 128])
+@pytest.mark.parametrize("sign", [1, -1])
+def test_scores_at_the_bound(sign, head_dim, cross, monkeypatch):
+    """The largest gains that the kernel without a maximum takes (bound just under 64), all scores near it or near minus
+    it: probabilities of 2^50 to 2^64, or their reciprocals."""
+    w, blob, _, _, bound = _lean_workload(head_dim, cross, 1.955 if head_dim == 128 else 2.325, sign)
+    assert 63 < bound <= 64
+    sc = _Scores(monkeypatch)
+    _run(w, blob)
+    assert 50 < (sc.hi if sign > 0 else -sc.lo) < 64
+
+
+@pytest.mark.parametrize("cross", [False, True])
+@pytest.mark.parametrize("head_dim", [64, 128])
+@pytest.mark.parametrize("sign", [1, -1])
+def test_scores_past_the_range(sign, head_dim, cross, monkeypatch):
+    """Probabilities of 2^140 and more, or of less than 2^-150 for every key: an unsubtracted 2^s is infinite, or their sum 0."""
+    w, blob, _, _, bound = _lean_workload(head_dim, cross, 3.4 if head_dim == 128 else 4.1, sign)
+    assert bound > 64
+    sc = _Scores(monkeypatch)
+    _run(w, blob)
+    assert sc.hi > 140 if sign > 0 else sc.row_max < -150
+
+
+def test_rotated_scores_past_the_range(monkeypatch):
+    """Gains of 3.4 in the even and 1 / 3.4 in the odd dimensions of q, the reverse in k: products of 1 in every dimension (a
+    bound of 16.6), but queries along the even and keys along the odd dimensions meet under a rotation, at 2^140 and more."""
+    w = _workload(150, 128, rope=1, rope_theta=1.01)  # every pair turns by about the same angle
+    blob = _weights(w.model, 1.0)
+    t = synth.split_block_weights(w.model, blob, 0)
+    for name, even in (("q", 3.4), ("k", 1 / 3.4)):
+        t["g" + name][0::2], t["g" + name][1::2] = even, 1 / even
+        t["b" + name][0::2], t["b" + name][1::2] = (4.0, 0.0) if name == "q" else (0.0, 4.0)
+    sc = _Scores(monkeypatch)
+    _run(w, blob)
+    assert sc.hi > 140
 
 
 @pytest.mark.parametrize("cross", [False, True])
@@ -139,12 +190,7 @@ class _Scores:
 def test_value_range(sign, head_dim, cross, monkeypatch):
     """All scores near 50 with values of 2^105, or near -50 with values of 2^-105: the products leave the range of a float
     unless the row's maximum is subtracted, which the bound on the values decides."""
-    w = _workload(150, head_dim, cond_len=70 if cross else 0)
-    g = 1.9 if head_dim == 128 else 2.25
-    blob = _weights(w.model, 1.0 if cross else g, g)
-    t = synth.split_block_weights(w.model, blob, 0)
-    s = "_c" if cross else ""
-    _lean(t, sign if cross else -sign, s)  # (the gains of k have the other sign)
+    w, blob, t, s, _ = _lean_workload(head_dim, cross, 1.9 if head_dim == 128 else 2.25, sign)
     for name, scale in (("wv", 2.0 ** (105 * sign)), ("bv", 2.0 ** (105 * sign)), ("wo", 2.0 ** (-105 * sign))):
         t[name + s] *= scale
     sc = _Scores(monkeypatch)
