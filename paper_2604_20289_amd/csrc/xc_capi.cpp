@@ -174,6 +174,9 @@ namespace {
 // largest visible key window (W_kv x L) and largest per-kind column-sum
 // partial buffer (bytes) whose kernel offsets fit in 32 bits
 constexpr long long kMaxWindowKeys = 1ll << 24;
+// the attention kernels' unsigned V^T byte offset: up to 127 rows of Lcap bf16
+// keys and a 64-key tile
+static_assert(127 * kMaxWindowKeys * 2 + 128 < (1ll << 32), "V^T staging offsets");
 constexpr long long kMaxPartialBytes = (1ll << 31) - 1;
 
 bool gateable(const xc_handle* h, int b) {
@@ -222,9 +225,9 @@ xc_status validate_model(const xc_model_config* m) {
   const long long L = tokens_of(m);
   if (L < 1 || L > (1ll << 24)) return XC_ERR_INVALID_ARG;
   if ((long long)m->kv_window * L > (1ll << 28)) return XC_ERR_INVALID_ARG;
-  // shapes whose 32-bit kernel offsets would wrap: the attention kernel's
-  // per-thread V^T staging offset spans up to 63 rows of Lcap keys (bf16),
-  // the MLP-down epilogue's column-sum partials ceil(L/32) x 2 x C floats
+  // shapes whose 32-bit kernel offsets would wrap: the attention kernels'
+  // V^T staging offset, the MLP-down epilogue's column-sum partials of
+  // ceil(L/32) x 2 x C floats
   if ((long long)m->kv_window * L > kMaxWindowKeys) return XC_ERR_UNSUPPORTED;
   if ((L + 31) / 32 * 2 * (long long)m->hidden * 4 > kMaxPartialBytes) return XC_ERR_UNSUPPORTED;
   if (m->dtype == XC_BF16) {
