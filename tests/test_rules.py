@@ -61,23 +61,6 @@ def test_attention_wide_waves():
         assert not wide(*case, 256), case
 
 
-def test_attention_splits():
-    """Split wherever a split measured faster, whole where it did not ((items, key tiles) on 256 CUs), and never past what the
-    workspace holds."""
-    n = rules.lib().splits
-    for case in ((16, 8), (36, 8), (36, 9), (48, 10), (64, 9), (64, 12), (112, 14), (128, 16), (336, 330), (24, 48), (4, 10)):
-        assert n(*case, 256, 1 << 40) > 1, case
-    for case in ((1, 7), (16, 7), (48, 7), (84, 8), (112, 10), (128, 10), (208, 102), (256, 64), (570, 32)):
-        assert n(*case, 256, 1 << 40) == 1, case
-    for items in (1, 4, 24, 60, 336):
-        for tiles in (1, 7, 8, 10, 33, 330):
-            free = n(items, tiles, 256, 1 << 40)
-            assert 1 <= free <= max(1, min(16, tiles // 2))
-            for most in range(0, 18):
-                assert n(items, tiles, 256, most) <= max(most, 1)
-            assert n(items, tiles, 256, free) == free
-
-
 @pytest.mark.parametrize("action", [0.5, 40.0])
 def test_value_bounds_hold(action):
     """Against the largest value that the oracle's block and cross-attention store; within a factor of 200 of it."""
@@ -112,20 +95,6 @@ def test_adaln_wave_rows():
     for n, chunks in ((73728, 9), (61440, 18), (122880, 18), (368640, 18), (147456, 24), (147456, 30), (73728, 33), (368640, 34),
                       (98304, 50)):
         assert rows(n, chunks) == 32, (n, chunks)
-
-
-def test_gemm_f32_tiles():
-    """The tile that measured fastest (M, N, K on 256 CUs), and both tiles' edges."""
-    tile = rules.lib().f32_tile
-    for want, cases in ((16, ((64, 384, 128), (64, 1024, 1024), (200, 512, 512), (512, 256, 1024), (700, 256, 256), (1100, 256, 64))),
-                        (32, ((200, 768, 3072), (300, 768, 768), (512, 512, 512), (2048, 256, 256), (700, 3072, 1024),
-                              (2048, 1536, 1536), (4096, 1024, 1024))),
-                        (64, ((2048, 2304, 768), (4096, 1536, 512), (4096, 4608, 1536)))):
-        for c in cases:
-            assert tile(*c, 256) == want, c
-    assert (tile(16, 8192, 512, 256), tile(16, 8193, 512, 256)) == (16, 32)
-    assert (tile(16, 24576, 508, 256), tile(16, 24577, 508, 256)) == (16, 32)
-    assert (tile(4096, 1024, 4, 256), tile(4096, 1025, 4, 256)) == (32, 64)
 
 
 def test_f32_attention_waves():
