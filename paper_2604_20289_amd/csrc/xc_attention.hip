@@ -18,7 +18,8 @@
 //     denominator sums the bf16 probabilities that the P.V product consumes;
 //     accumulation is float.
 // Two kernels: attn_bounded_kernel where the RMSNorm gains bound the scores
-// (no running maximum), attn_bf16_kernel otherwise.
+// (no running maximum) and its wider waves pay (attention_bounded,
+// attention_wide_waves), attn_bf16_kernel otherwise.
 // fp32 path: one workgroup per (query, head), plain online softmax.
 #include "xc_internal.h"
 #include "xc_rules.h"
@@ -96,8 +97,9 @@ __device__ __forceinline__ float partner_sum(float x) {
 // over the XCDs, so workgroup b takes unit (b mod 8) * per_xcd + b / 8): the
 // workgroups resident on one XCD then stream the same key/value chunk of one
 // head at about the same time.  With S = 1 a unit writes the normalised
-// output; otherwise it leaves (O unnormalised, running max, running sum) in
-// the workspace and the merge kernel combines the S pieces of each item.
+// output; otherwise it leaves its own normalised output with its running max
+// and sum in the workspace and the merge kernel combines the S pieces of each
+// item.
 //
 // attn_bf16_kernel, any scores (online softmax): 8 waves of 32 queries, two
 // per SIMD.  Software pipeline, per wave and key tile j:
@@ -987,37 +989,12 @@ int resident_attention_groups() {
   return groups[dev];
 }
 
-// Key splits per item.  Estimated time in key-tile steps of one resident
-// workgroup: rounds * (tiles per unit + 4 for the unit's prologue and
-// epilogue) + 4 S items / (resident workgroups) for the merge (fitted to
-// measured split sweeps on the multi-camera shapes, where it picks S = 3) + 5
-// for the merge's launch, which a skipped block also pays (1.8 us), over S <=
-// 16 with chunks of at least 2 tiles.  Up to 7 key tiles stay whole: 400
-// tokens, 8 heads of 64, 5 / 7 / 8 tiles 13.6 / 14.9 / 15.6 us whole, 14.0 /
-// 14.6 / 14.6 in three splits; 12 heads of 128 19.0 / 20.9 / 22.1 and 18.4 /
-// 19.4 / 19.5; 4186 tokens, 8 heads of 128 (136 items, past one round when
-// split) 20.5 / 22.9 / 24.4 and 32 / 36 / 37.  Few items take more splits
-// (768 tokens, 8 heads, 3072 keys, 24 items: 10 splits 19.3 us, 5 splits 21.4,
-// none 47; 300 tokens, 2 heads, 600 keys: 5 splits 18.3 us, 2 splits 21.0); only split
-// counts whose partials fit in cap_floats workspace floats are considered
-// (S = 1 needs none).
+// Key splits per item, among those whose partials fit in cap_floats workspace
+// floats (one needs none).
 int attention_splits(int L, int Lk, int H, int D, size_t cap_floats) {
-  const int items = H * ((L + kQT - 1) / kQT);
-  const int NT = (Lk + 63) / 64;
-  const int slots = resident_attention_groups();
-  int best = 1;
-  double best_cost = 1e300;
-  for (int s = 1; s <= 16 && (s == 1 || NT / s >= 2); ++s) {
-    if (s > 1 && (size_t)items * s * (size_t)piece_floats(D) > cap_floats) break;
-    const long long units = (long long)items * s;
-    const long long rounds = (units + slots - 1) / slots;
-    const double cost = (double)rounds * ((double)NT / s + 4.0) + (s > 1 ? 5.0 + 4.0 * s * items / slots : 0.0);
-    if (cost < best_cost - 1e-9) {
-      best_cost = cost;
-      best = s;
-    }
-  }
-  return best;
+  const long long items = (long long)H * ((L + kQT - 1) / kQT);
+  const long long most = (long long)(cap_floats / ((size_t)items * (size_t)piece_floats(D)));
+  return attention_split_count(items, (Lk + 63) / 64, resident_attention_groups(), most);
 }
 
 size_t attention_workspace_floats(int L, int Lk, int H, int D) {

@@ -103,6 +103,32 @@ inline bool attention_wide_waves(int L, long long Lk, int D, long long items, in
   return tiles != 2 || (D == 64 && items > cus);
 }
 
+// Key splits of the bf16 attention (at most `most`) for `items` (head, 256-query)
+// items of `tiles` key tiles on `slots` resident workgroups.  Estimated time in
+// key-tile steps (1.2 us at 128 head dims, 0.8 at 64): rounds * (tiles per unit +
+// 4 for the unit's prologue and epilogue) + 1.5 + 5 S items / slots for the
+// merge, over S <= 16 with at least 2 tiles each.  Up to 7 tiles stay whole: a
+// split gains at most 1.3 us there and a skipped block would pay 1.8 for the
+// merge's launch.  us with 1 / 2 / 3 / 4 / 5 / 8 splits:
+//   128 dims, 24 items: 7 tiles 21.1 / 20.9 / 20.1 / 19.5 / 20.4 / -, 8 tiles 22.1 / 21.1 / 20.2 / 19.5 / 20.2 / 19.1
+//   128 dims, 64 items: 8 tiles 23.1 / 22.2 / 22.3 / 23.5 / 31 / 34, 12 tiles 27.2 / 24.9 / 24.0 / 24.9 / 36 / 38
+//   128 dims, 112 items: 8 tiles 25.2 / 27.1 / 38, 12 tiles 30.7 / 30.2 / 42, 16 tiles 36.6 / 33.5 / 47
+//   64 dims, 24 items: 8 tiles 15.7 / 15.6 / 15.3 / 15.2 / 15.6 / 16.0, 16 tiles 22.1 / 18.8 / 17.7 / 16.9 / 17.3 / 17.7,
+//     48 tiles - / 31.7 / 26.2 / 23.9 / 22.6 / 21.6 (10: 21.8, 12: 27.1)
+inline int attention_split_count(long long items, long long tiles, long long slots, long long most) {
+  int best = 1;
+  double best_cost = 1e300;
+  for (int s = 1; s <= 16 && (s == 1 || (tiles >= 8 && tiles / s >= 2 && s <= most)); ++s) {
+    const long long rounds = (items * s + slots - 1) / slots;
+    const double cost = (double)rounds * ((double)tiles / s + 4.0) + (s > 1 ? 1.5 + 5.0 * s * items / slots : 0.0);
+    if (cost < best_cost - 1e-9) {
+      best_cost = cost;
+      best = s;
+    }
+  }
+  return best;
+}
+
 // Tile of a bf16 M x N x K product on `cus` CUs.  Times are estimated in
 // microseconds as rounds * (fixed + K / 64 * stage), the constants fitted to
 // launches of every tile at 300 to 12096 rows, N and K 256 to 8192 (output and

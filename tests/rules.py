@@ -29,6 +29,9 @@ double cross_bound(const float* wv, const float* bv, int C, double cond_max) {
 int wave_rows(long long rows, int chunks) { return adaln_wave_rows(rows, chunks); }
 int f32_waves(long long Lk) { return attention_f32_waves(Lk); }
 int wide_waves(int L, long long Lk, int D, long long items, int cus) { return attention_wide_waves(L, Lk, D, items, cus); }
+int splits(long long items, long long tiles, long long slots, long long most) {
+  return attention_split_count(items, tiles, slots, most);
+}
 int tile(int M, int N, int K, int C, int cus) { return pick_tile(M, N, K, C, cus); }
 int bounded(float score, double value, long long Lk) { return attention_bounded(score, value, Lk); }
 }
@@ -48,7 +51,8 @@ def lib():
     p = np.ctypeslib.ndpointer(np.float32, flags="C_CONTIGUOUS")
     for name, res, args in (("score_bound", f, [p, p, i, i]), ("self_bound", d, [p, p, p, p, i, i, d]),
                             ("cross_bound", d, [p, p, i, d]), ("bounded", i, [f, d, ll]), ("wave_rows", i, [ll, i]),
-                            ("f32_waves", i, [ll]), ("tile", i, [i, i, i, i, i]), ("wide_waves", i, [i, ll, i, ll, i])):
+                            ("f32_waves", i, [ll]), ("tile", i, [i, i, i, i, i]), ("splits", i, [ll, ll, ll, ll]),
+                            ("wide_waves", i, [i, ll, i, ll, i])):
         getattr(out, name).restype, getattr(out, name).argtypes = res, args
     return out
 

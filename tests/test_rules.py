@@ -61,6 +61,23 @@ def test_attention_wide_waves():
         assert not wide(*case, 256), case
 
 
+def test_attention_splits():
+    """Split wherever a split measured faster, whole where it did not ((items, key tiles) on 256 CUs), and never past what the
+    workspace holds."""
+    n = rules.lib().splits
+    for case in ((16, 8), (36, 8), (36, 9), (48, 10), (64, 9), (64, 12), (112, 14), (128, 16), (336, 330), (24, 48), (4, 10)):
+        assert n(*case, 256, 1 << 40) > 1, case
+    for case in ((1, 7), (16, 7), (48, 7), (84, 8), (112, 10), (128, 10), (208, 102), (256, 64), (570, 32)):
+        assert n(*case, 256, 1 << 40) == 1, case
+    for items in (1, 4, 24, 60, 336):
+        for tiles in (1, 7, 8, 10, 33, 330):
+            free = n(items, tiles, 256, 1 << 40)
+            assert 1 <= free <= max(1, min(16, tiles // 2))
+            for most in range(0, 18):
+                assert n(items, tiles, 256, most) <= max(most, 1)
+            assert n(items, tiles, 256, free) == free
+
+
 @pytest.mark.parametrize("action", [0.5, 40.0])
 def test_value_bounds_hold(action):
     """Against the largest value that the oracle's block and cross-attention store; within a factor of 200 of it."""
