@@ -1053,22 +1053,12 @@ void launch_bf16(const void* A, const void* W, int M, int N, int K, const EpiArg
 
 template <int MODE>
 void launch_f32(const void* A, const void* W, int M, int N, int K, const EpiArgs& e, const int* flag, hipStream_t st) {
-  // 16-byte rows; the operands are re-read by every tile, so the tiles grow
-  // with the product, up to the staged 64 x 64 ones
-  const long long t16 = (long long)((M + 15) / 16) * ((N + 15) / 16);
   const bool rows16 = K % 4 == 0 && ((reinterpret_cast<unsigned long long>(A) | reinterpret_cast<unsigned long long>(W)) & 15) == 0;
-  if (rows16 && t16 <= 4ll * cu_count()) {
-    dim3 grid((N + 15) / 16, (M + 15) / 16);
-    gemm_f32_small<MODE, 1><<<grid, 256, 0, st>>>((const float*)A, (const float*)W, M, N, K, e, flag);
-    return;
-  }
-  if (rows16 && t16 <= 32ll * cu_count()) {
-    dim3 grid((N + 31) / 32, (M + 31) / 32);
-    gemm_f32_small<MODE, 2><<<grid, 256, 0, st>>>((const float*)A, (const float*)W, M, N, K, e, flag);
-    return;
-  }
-  dim3 grid((N + 63) / 64, (M + 63) / 64);
-  gemm_f32_kernel<MODE><<<grid, 256, 0, st>>>((const float*)A, (const float*)W, M, N, K, e, flag);
+  const int t = rows16 ? gemm_f32_tile(M, N, K, cu_count()) : 64;
+  const dim3 grid((N + t - 1) / t, (M + t - 1) / t);
+  if (t == 16) gemm_f32_small<MODE, 1><<<grid, 256, 0, st>>>((const float*)A, (const float*)W, M, N, K, e, flag);
+  else if (t == 32) gemm_f32_small<MODE, 2><<<grid, 256, 0, st>>>((const float*)A, (const float*)W, M, N, K, e, flag);
+  else gemm_f32_kernel<MODE><<<grid, 256, 0, st>>>((const float*)A, (const float*)W, M, N, K, e, flag);
 }
 
 }  // namespace

@@ -172,6 +172,21 @@ inline int pick_tile(int M, int N, int K, int C, int cus) {
   return best;
 }
 
+// Tile (16, 32 or the staged 64 square) of a float32 M x N x K product with
+// 16-byte rows on `cus` CUs.  Every tile re-reads its operands, so the tiles grow
+// with the product; a long K makes the 16-square ones re-read more.  us with 16 /
+// 32 / 64 by the number of 16-square tiles (256 CUs):
+//   K = 1024: 256 9.3 / 15.2 / 145, 512 12.4 / 15.0 / 140, 704 17.0 / 15.4 / 141, 832 19.7 / 15.7 / 119, 1104
+//     23.3 / 25.6 / 140, 2048 34.0 / 26.6 / 141
+//   K = 256: 512 6.8 / 8.2 / 39, 704 7.7 / 8.2 / 41, 1104 9.6 / 10.1 / 42, 1536 10.1 / 9.5 / 41, 2048 12.6 / 10.4 / 42
+//   K = 128: 1056 7.1 / 7.9 / 22, 1408 8.8 / 8.9 / 22, 2048 9.6 / 8.7 / 23
+//   8448 x K 1024: 121 / 93 / 145, 12288 x 1536: 261 / 202 / 262, 16384 x 1024: 232 / 180 / 192, 18432 x 768: 196 /
+//     151 / 145, 24576 x 1024: 343 / 255 / 221
+inline int gemm_f32_tile(int M, int N, int K, int cus) {
+  const long long t16 = (long long)((M + 15) / 16) * ((N + 15) / 16);
+  return t16 <= (K >= 512 ? 2 : 6) * (long long)cus ? 16 : t16 <= 64ll * cus ? 32 : 64;
+}
+
 // Waves of a float32 attention workgroup (one query of one head): no more than
 // the keys have 64-key chunks, the others would only cost the launch (3000
 // queries, 8 heads of 32, 20 keys: four waves 54.2 us, one 27.1; 4096 queries, 2

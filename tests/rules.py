@@ -32,6 +32,7 @@ int wide_waves(int L, long long Lk, int D, long long items, int cus) { return at
 int splits(long long items, long long tiles, long long slots, long long most) {
   return attention_split_count(items, tiles, slots, most);
 }
+int f32_tile(int M, int N, int K, int cus) { return gemm_f32_tile(M, N, K, cus); }
 int tile(int M, int N, int K, int C, int cus) { return pick_tile(M, N, K, C, cus); }
 int bounded(float score, double value, long long Lk) { return attention_bounded(score, value, Lk); }
 }
@@ -52,7 +53,7 @@ def lib():
     for name, res, args in (("score_bound", f, [p, p, i, i]), ("self_bound", d, [p, p, p, p, i, i, d]),
                             ("cross_bound", d, [p, p, i, d]), ("bounded", i, [f, d, ll]), ("wave_rows", i, [ll, i]),
                             ("f32_waves", i, [ll]), ("tile", i, [i, i, i, i, i]), ("splits", i, [ll, ll, ll, ll]),
-                            ("wide_waves", i, [i, ll, i, ll, i])):
+                            ("f32_tile", i, [i, i, i, i]), ("wide_waves", i, [i, ll, i, ll, i])):
         getattr(out, name).restype, getattr(out, name).argtypes = res, args
     return out
 

@@ -10,13 +10,14 @@ import synth
 torch = pytest.importorskip("torch")
 pytestmark = pytest.mark.gpu
 
-# name: (hidden, heads, mlp, kv_window, grid).  Tiles of 16 x 16 on 256 CUs: up to 1024 take
-# 16-square tiles, up to 8192 32-square ones (h256-L300: output 304, QKV 912, MLP 1216;
-# h512-L1100: output 2208, QKV 6624, MLP up 8832 on 64 x 64)
+# name: (hidden, heads, mlp, kv_window, grid).  Tiles of 16 x 16 on 256 CUs: up to 1536 (512 with K of 512 and more) take
+# 16-square tiles, up to 16384 32-square ones (h256-L300: output 304, QKV 912, MLP up 1216, MLP down 304;
+# h512-L1100: output 2208, QKV 6624, MLP up 8832; h512-L2050: QKV 12384, MLP up 17028 on 64 x 64)
 MODELS = {
     "h128-L64": (128, 4, 512, 2, (1, 4, 4, 4)),
     "h256-L300": (256, 4, 1024, 2, (2, 3, 5, 10)),
     "h512-L1100": (512, 8, 2048, 1, (1, 1, 25, 44)),
+    "h512-L2050": (512, 8, 2112, 1, (1, 1, 41, 50)),
     "h84-d28-mlp52": (84, 3, 52, 3, (1, 1, 7, 11)),       # K = 84 and 52: part of a 16-deep chunk
     "h12-d6-mlp30": (12, 2, 30, 2, (1, 1, 3, 11)),        # rows of no multiple of 16 bytes (MLP down, heads)
     "h128-d128-L20": (128, 1, 130, 4, (1, 1, 4, 5)),      # one head of 128, 20 to 80 keys

@@ -114,6 +114,20 @@ def test_adaln_wave_rows():
         assert rows(n, chunks) == 32, (n, chunks)
 
 
+def test_gemm_f32_tiles():
+    """The tile that measured fastest (M, N, K on 256 CUs), and both tiles' edges."""
+    tile = rules.lib().f32_tile
+    for want, cases in ((16, ((64, 384, 128), (64, 1024, 1024), (200, 512, 512), (512, 256, 1024), (700, 256, 256), (1100, 256, 64))),
+                        (32, ((200, 768, 3072), (300, 768, 768), (512, 512, 512), (2048, 256, 256), (700, 3072, 1024),
+                              (2048, 1536, 1536), (4096, 1024, 1024))),
+                        (64, ((2048, 2304, 768), (4096, 1536, 512), (4096, 4608, 1536)))):
+        for c in cases:
+            assert tile(*c, 256) == want, c
+    assert (tile(16, 8192, 512, 256), tile(16, 8193, 512, 256)) == (16, 32)
+    assert (tile(16, 24576, 508, 256), tile(16, 24577, 508, 256)) == (16, 32)
+    assert (tile(4096, 1024, 4, 256), tile(4096, 1025, 4, 256)) == (32, 64)
+
+
 def test_f32_attention_waves():
     assert [rules.lib().f32_waves(k) for k in (1, 64, 65, 128, 129, 1 << 24)] == [1, 1, 2, 2, 4, 4]
 
