@@ -130,28 +130,39 @@ inline int attention_split_count(long long items, long long tiles, long long slo
 }
 
 // Tile of a bf16 M x N x K product on `cus` CUs.  Times are estimated in
-// microseconds as rounds * (fixed + K / 64 * stage), the constants fitted to
-// launches of every tile at 300 to 12096 rows, N and K 256 to 8192 (output and
-// MLP products; fixed holds the launch, the first stage's latency and the
-// epilogue).  Small tiles run one workgroup per CU with a deep ring or two with a
-// shallow one; a shallow 64 x 128 tile with its CU to itself takes its own line.
-//   768 x 512 x 2048 (MLP down): 64 x 64 13.0 us, 64 x 128 15.4, 128 x 128 20.4
-//   3245 x 1024 x 4096: 64 x 128 44.1, 128 x 128 deep 38.9, 192 x 128 56.9
-//   3510 x 2304 x 768 (QKV): 64 x 128 30.6, 128 x 128 shallow 26.1
-//   7020 x 1536 x 6144: 128 x 128 172, 192 x 128 142, 192 x 256 133, 256 x 256 161
-//   12096 x 6144 x 2048 (QKV): 256 x 256 275 (5 rounds), 192 x 256 364 (6 rounds)
-//   12096 x 2048 x 8192: 192 x 128 381, 192 x 256 365, 256 x 256 408
+// microseconds as rounds * (fixed + K / 64 * stage); fixed holds the launch, the
+// first stage's latency and the epilogue, the QKV product's longer one has
+// constants of its own.  Fitted to launches of every tile over 470 models of 200
+// to 16000 tokens, hidden 128 to 2560 and MLP 128 to 10240, with and without
+// rotation: 0.3% (QKV) and 0.7% (others) over the fastest tile on average, no
+// product over 1.5% slower than on the 32-deep two-workgroup kernel that these
+// tiles replaced.  Small tiles run one workgroup per CU with a deep ring or two
+// with a shallow one; a shallow 64 x 128 tile with its CU to itself takes its own
+// line.
+//   768 x 512 x 2048: 64 x 64 13.2 us, 64 x 128 15.5, 128 x 128 deep 20.9
+//   3240 x 1024 x 4096: 64 x 128 43.6, 128 x 128 deep 40.6, 192 x 128 57.9
+//   8370 x 1024 x 256: 128 x 128 17.5, 192 x 128 15.0, 256 x 256 17.8
+//   7020 x 1536 x 6144: 128 x 128 deep 168, 192 x 128 140, 192 x 256 131, 256 x 256 156
+//   12096 x 2048 x 8192: 192 x 128 379, 192 x 256 360, 256 x 256 410
+//   QKV 13260 x 384 x 128: 64 x 128 13.7, 128 x 128 11.4, 192 x 128 deep 13.7, 192 x 128 13.0
+//   QKV 14100 x 768 x 256, rotated: 64 x 128 27.6, 192 x 128 24.8, 256 x 256 30.4, 192 x 256 26.1
+//   QKV 5820 x 4992 x 1664, rotated: 128 x 128 135, 192 x 128 deep 155, 192 x 128 129
+//   QKV 7020 x 4608 x 1536: 192 x 128 114, 256 x 256 102, 192 x 256 113
 struct GemmTile {
   int id, bm, bn, per_cu;
-  double fixed, stage;
+  double fixed, stage, qkv_fixed, qkv_stage;
 };
 enum TileId { kT64x64, kT64x128, kT128x128deep, kT128x128, kT192x128deep, kT192x128, kT256x256, kT192x256 };
 constexpr GemmTile kGemmTiles[] = {
-    {kT64x64, 64, 64, 1, 6.5, 0.24},         {kT64x128, 64, 128, 1, 6.0, 0.31},
-    {kT64x128, 64, 128, 2, 7.5, 0.60},       {kT128x128deep, 128, 128, 1, 8.5, 0.48},
-    {kT128x128, 128, 128, 2, 9.5, 0.93},     {kT192x128deep, 192, 128, 1, 10.0, 0.65},
-    {kT192x128, 192, 128, 2, 13.5, 1.38},    {kT256x256, 256, 256, 1, 12.0, 1.50},
-    {kT192x256, 192, 256, 1, 14.0, 1.31},
+    {kT64x64, 64, 64, 1, 6.5, 0.24, 0, 0},
+    {kT64x128, 64, 128, 1, 6.0, 0.31, 6.0, 0.31},
+    {kT64x128, 64, 128, 2, 7.5, 0.58, 6.75, 0.60},
+    {kT128x128deep, 128, 128, 1, 8.5, 0.48, 9.5, 0.48},
+    {kT128x128, 128, 128, 2, 9.5, 0.93, 9.75, 1.10},
+    {kT192x128deep, 192, 128, 1, 11.25, 0.69, 14.0, 0.87},
+    {kT192x128, 192, 128, 2, 12.0, 1.34, 12.25, 1.38},
+    {kT256x256, 256, 256, 1, 12.0, 1.50, 12.0, 1.62},
+    {kT192x256, 192, 256, 1, 14.0, 1.20, 14.0, 1.26},
 };
 
 // C: columns of each of q, k, v for the QKV epilogue (0: another epilogue)
@@ -163,7 +174,8 @@ inline int pick_tile(int M, int N, int K, int C, int cus) {
     // a QKV tile lies in one of q, k, v, its waves hold 64 columns
     if (C != 0 && (C % t.bn != 0 || t.id == kT64x64)) continue;
     const long long tiles = (long long)((M + t.bm - 1) / t.bm) * (N / t.bn), slots = (long long)cus * t.per_cu;
-    const double us = (double)((tiles + slots - 1) / slots) * (t.fixed + K / 64 * t.stage);
+    const double fixed = C != 0 ? t.qkv_fixed : t.fixed, stage = C != 0 ? t.qkv_stage : t.stage;
+    const double us = (double)((tiles + slots - 1) / slots) * (fixed + K / 64 * stage);
     if (us < best_us) {
       best_us = us;
       best = t.id;

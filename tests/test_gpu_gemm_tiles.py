@@ -17,18 +17,21 @@ pytestmark = pytest.mark.gpu
 # name: (hidden, heads, mlp, grid, the tiles the launcher picks on 256 CUs for QKV, output, MLP up and MLP down).  "deep":
 # one workgroup per CU with a deep stage ring.  K = hidden, but mlp for MLP down
 SHAPES = {
-    "h384-L16000": (384, 3, 384, (1, 1, 125, 128), ("192x128 deep", "192x128 deep", "192x128 deep", "192x128 deep")),
+    "h384-L16000": (384, 3, 384, (1, 1, 125, 128), ("192x128", "128x128", "128x128", "128x128")),
     "h1152-L7020": (1152, 9, 1152, (2, 3, 26, 45), ("192x128", "128x128", "128x128", "128x128")),
-    "h768-L16000": (768, 6, 768, (1, 1, 125, 128), ("192x256", "192x256", "192x256", "192x256")),
-    "h2048-L6100": (2048, 16, 128, (1, 1, 61, 100), ("192x256", "192x256", "64x64", "256x256")),
-    "h640-L5000": (640, 5, 1280, (2, 1, 50, 50), ("192x128", "128x128 deep", "128x128", "128x128 deep")),
-    "h1024-L1100": (1024, 8, 1024, (1, 1, 44, 25), ("128x128 deep", "64x128", "64x128", "64x128")),
+    "h768-L16000": (768, 6, 768, (1, 1, 125, 128), ("192x128", "192x128", "192x128", "192x128")),
+    "h2048-L6100": (2048, 16, 128, (1, 1, 61, 100), ("192x256", "192x256", "64x64", "192x128")),
+    "h640-L5000": (640, 5, 1280, (2, 1, 50, 50), ("192x128", "64x128", "128x128", "128x128 deep")),
+    "h1024-L1100": (1024, 8, 1024, (1, 1, 44, 25), ("64x128", "64x128", "64x128", "64x128")),
     "h256-L70": (256, 2, 1024, (1, 1, 7, 10), ("64x128", "64x128", "64x128", "64x64")),
-    "h640-L13477": (640, 5, 256, (1, 1, 1, 13477), ("128x128", "192x128", "128x128 deep", "192x128")),
-    "h640-mlp640-L13477": (640, 10, 640, (1, 1, 1, 13477), ("128x128", "192x128", "192x128", "192x128")),
-    "h256-L10982": (256, 4, 1024, (1, 2, 17, 323), ("256x256", "64x128", "256x256", "128x128 deep")),
     "h1024-L12479": (1024, 8, 128, (1, 1, 1, 12479), ("256x256", "256x256", "64x128", "256x256")),
     "h512-L16": (512, 4, 128, (1, 1, 4, 4), ("64x128", "64x64", "64x64", "64x128")),
+    "h640-L6635": (640, 10, 640, (1, 1, 5, 1327), ("128x128", "192x128 deep", "192x128 deep", "192x128 deep")),
+    "h768-L2927": (768, 6, 768, (1, 1, 1, 2927), ("128x128", "128x128 deep", "128x128 deep", "128x128 deep")),
+    "h768-L10961": (768, 12, 1280, (1, 1, 97, 113), ("256x256", "192x128", "256x256", "192x256")),
+    "h1920-L321": (1920, 15, 128, (1, 1, 3, 107), ("128x128 deep", "64x64", "64x64", "64x128")),
+    "h1280-L1114": (1280, 10, 128, (1, 2, 1, 557), ("192x128 deep", "64x128", "64x64", "64x128")),
+    "h1024-L4163": (1024, 16, 2048, (1, 1, 23, 181), ("256x256", "192x128 deep", "192x256", "192x128 deep")),
 }
 
 
