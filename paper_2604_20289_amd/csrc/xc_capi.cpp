@@ -454,15 +454,17 @@ P* wptr(void* base, size_t elems_before, size_t esz) {
   return reinterpret_cast<P*>(reinterpret_cast<char*>(base) + elems_before * esz);
 }
 
-// Which attention kernel the (cross-)attention of block b takes (bf16 models;
-// see attention_bounded).
+// Which attention kernel the (cross-)attention of block b takes (see
+// attention_bounded); only bf16 models have the choice and the rows' bounds.
 bool self_bounded(const xc_handle* h, int b, long long Lk) {
-  return attention_bounded(h->score_bound[b],
+  return h->dtype == XC_BF16 &&
+         attention_bounded(h->score_bound[b],
                            self_value_bound(h->mod_rows[b], h->v_rows[b], h->C, h->Dc, h->cond_max), Lk);
 }
 
 bool cross_bounded(const xc_handle* h, int b) {
-  return attention_bounded(h->score_bound_c[b], cross_value_bound(h->v_rows_c[b], h->C, h->token_max), h->n_cond);
+  return h->dtype == XC_BF16 &&
+         attention_bounded(h->score_bound_c[b], cross_value_bound(h->v_rows_c[b], h->C, h->token_max), h->n_cond);
 }
 
 // The largest magnitude a pass's conditioning has had since the last reset:
@@ -817,6 +819,32 @@ void free_all(xc_handle* h) {
   h->ev_free.clear();
 }
 
+// The row bounds of every block's shift / scale rows of W_ada and of its Wv,
+// from the uploaded weights (on the host the pass over them added 10 to 40% to a
+// model's set-up).
+void row_bounds(xc_handle* h) {
+  const int B = h->B, C = h->C, Dc = h->Dc;
+  const size_t CC = (size_t)C * C;
+  std::vector<double> out((size_t)3 * B * 2);
+  double* d_out = dalloc_t<double>(h, out.size());
+  XC_HIP(hipMemsetAsync(d_out, 0, out.size() * sizeof(double), h->st));
+  launch_row_bounds(h->w_ada, (long long)6 * C * Dc, h->b_ada, (long long)6 * C, 2 * C, Dc, B, d_out, h->st);
+  launch_row_bounds(wptr<void>(h->wqkv, 2 * CC, h->esz), 3 * (long long)CC, h->bqkv + 2 * C, (long long)3 * C, C, C, B,
+                    d_out + 2 * B, h->st);
+  if (h->Mc > 0)
+    launch_row_bounds(wptr<void>(h->wqkv_c, 2 * CC, h->esz), 3 * (long long)CC, h->bqkv_c + 2 * C, (long long)3 * C, C, C,
+                      B, d_out + 4 * B, h->st);
+  XC_HIP(hipGetLastError());
+  XC_HIP(hipMemcpyAsync(out.data(), d_out, out.size() * sizeof(double), hipMemcpyDeviceToHost, h->st));
+  XC_HIP(hipStreamSynchronize(h->st));
+  std::vector<RowBound>* to[3] = {&h->mod_rows, &h->v_rows, &h->v_rows_c};
+  for (int k = 0; k < 3; ++k)
+    for (int b = 0; b < B; ++b) {
+      const double* o = out.data() + ((size_t)k * B + b) * 2;
+      to[k]->push_back({std::sqrt(o[0]), o[1]});
+    }
+}
+
 void init_device(xc_handle* h, const float* w) {
   const int B = h->B, C = h->C, D = h->D, Dm = h->Dm, Dc = h->Dc, S = h->S, H = h->H;
   const size_t esz = h->esz;
@@ -851,17 +879,11 @@ void init_device(xc_handle* h, const float* w) {
   const size_t CC = (size_t)C * C;
   for (int b = 0; b < B; ++b) {
     upload(h, w + off, (size_t)6 * C * Dc, wptr<void>(h->w_ada, (size_t)b * 6 * C * Dc, esz), bf, stage);
-    h->mod_rows.emplace_back();
-    if (bf) h->mod_rows[b].add(w + off, w + off + (size_t)6 * C * Dc, (size_t)2 * C, Dc);
     off += (size_t)6 * C * Dc;
     upload(h, w + off, (size_t)6 * C, h->b_ada + (size_t)b * 6 * C, false, stage);
     off += (size_t)6 * C;
     for (int part = 0; part < 3; ++part) {  // Wq, bq, Wk, bk, Wv, bv
       upload(h, w + off, CC, wptr<void>(h->wqkv, (size_t)b * 3 * CC + part * CC, esz), bf, stage);
-      if (part == 2) {
-        h->v_rows.emplace_back();
-        if (bf) h->v_rows[b].add(w + off, w + off + CC, C, C);
-      }
       off += CC;
       upload(h, w + off, C, h->bqkv + (size_t)b * 3 * C + part * C, false, stage);
       off += C;
@@ -893,10 +915,6 @@ void init_device(xc_handle* h, const float* w) {
       off += C;
       for (int part = 0; part < 3; ++part) {  // Wq_c, bq_c, Wk_c, bk_c, Wv_c, bv_c
         upload(h, w + off, CC, wptr<void>(h->wqkv_c, (size_t)b * 3 * CC + part * CC, esz), bf, stage);
-        if (part == 2) {
-          h->v_rows_c.emplace_back();
-          if (bf) h->v_rows_c[b].add(w + off, w + off + CC, C, C);
-        }
         off += CC;
         upload(h, w + off, C, h->bqkv_c + (size_t)b * 3 * C + part * C, false, stage);
         off += C;
@@ -912,6 +930,8 @@ void init_device(xc_handle* h, const float* w) {
       off += D;
     }
   }
+
+  if (bf) row_bounds(h);
 
   h->kc = dalloc(h, (size_t)B * H * h->Lcap * D * esz);
   h->vt = dalloc(h, (size_t)B * H * h->Lcap * D * esz);

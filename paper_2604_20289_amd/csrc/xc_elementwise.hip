@@ -417,6 +417,28 @@ __global__ void fill_f32_kernel(float* p, float v, long long n) {
   for (long long i = blockIdx.x * 256ll + threadIdx.x; i < n; i += (long long)gridDim.x * 256) p[i] = v;
 }
 
+// Set-up only: a wave per row, the largest of its rows to out[2 b] (magnitudes of
+// doubles order as integers, NaN last).
+__global__ __launch_bounds__(256) void row_bounds_kernel(const bf16* __restrict__ w, long long w_stride,
+                                                         const float* __restrict__ bias, long long bias_stride, int rows,
+                                                         int cols, unsigned long long* __restrict__ out) {
+  const int lane = threadIdx.x & 63, b = blockIdx.y;
+  unsigned long long norm = 0, most = 0;
+  for (int r = blockIdx.x * 4 + (threadIdx.x >> 6); r < rows; r += gridDim.x * 4) {
+    const bf16* p = w + b * w_stride + (long long)r * cols;
+    double s = 0.0;
+    for (int i = lane; i < cols; i += 64) s += (double)(float)p[i] * (double)(float)p[i];
+    for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off, 64);
+    const double a = fabs((double)bias[b * bias_stride + r]);
+    norm = max(norm, __builtin_bit_cast(unsigned long long, fabs(s)));
+    most = max(most, __builtin_bit_cast(unsigned long long, a));
+  }
+  if (lane == 0) {
+    atomicMax(out + 2 * b, norm);
+    atomicMax(out + 2 * b + 1, most);
+  }
+}
+
 int grid_for(long long n, int per_block) {
   long long g = (n + per_block - 1) / per_block;
   if (g > 8192) g = 8192;
@@ -516,6 +538,13 @@ void launch_read_cache(int dtype, const void* src, float* out, int H, int R, int
 
 void launch_fill_f32(float* p, float v, long long n, hipStream_t st) {
   fill_f32_kernel<<<grid_for(n, 256 * 4), 256, 0, st>>>(p, v, n);
+}
+
+void launch_row_bounds(const void* w, long long w_stride, const float* bias, long long bias_stride, int rows, int cols,
+                       int n_blocks, double* out, hipStream_t st) {
+  const dim3 grid(min((rows + 3) / 4, 256), n_blocks);
+  row_bounds_kernel<<<grid, 256, 0, st>>>((const bf16*)w, w_stride, bias, bias_stride, rows, cols,
+                                          reinterpret_cast<unsigned long long*>(out));
 }
 
 }  // namespace xc

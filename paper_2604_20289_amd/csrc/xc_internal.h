@@ -190,6 +190,11 @@ void launch_fp_compare(const float* x, int C, const FpTables& t, float* fp0, flo
 void launch_gate_decide(const double* records, int n_wg, const GateArgs& ga, const GateState& gs, int sb, int b,
                         int evaluate, hipStream_t st);
 void launch_fill_f32(float* p, float v, long long n, hipStream_t st);
+// out[b] = max(out[b], {largest squared 2-norm of a bf16 row of w, largest
+// |bias|}) for n_blocks matrices of rows x cols (w and bias of block b at
+// multiples of the strides); out >= 0, a NaN is the largest value
+void launch_row_bounds(const void* w, long long w_stride, const float* bias, long long bias_stride, int rows, int cols,
+                       int n_blocks, double* out, hipStream_t st);
 // out [H][R][D] float32 from a model-dtype cache [H][Lcap][D] (transposed = 0)
 // or [H][D][Lcap] (transposed = 1), rows 0 .. R-1
 void launch_read_cache(int dtype, const void* src, float* out, int H, int R, int D, long long Lcap, int transposed,

@@ -37,19 +37,6 @@ inline float qk_score_bound(const float* gq, const float* gk, int D, bool rope) 
 // non-finite element make it infinite or NaN, which no rule accepts.
 struct RowBound {
   double norm = 0, bias = 0;
-  void add(const float* w, const float* b, size_t rows, size_t cols) {
-    for (size_t r = 0; r < rows; ++r) {
-      double s[4] = {0, 0, 0, 0};
-      const float* p = w + r * cols;
-      size_t i = 0;
-      for (; i + 4 <= cols; i += 4)
-        for (int k = 0; k < 4; ++k) s[k] += (double)p[i + k] * p[i + k];
-      for (; i < cols; ++i) s[0] += (double)p[i] * p[i];
-      const double n = std::sqrt((s[0] + s[1]) + (s[2] + s[3])), a = std::fabs((double)b[r]);
-      norm = n > norm || std::isnan(n) ? n : norm;
-      bias = a > bias || std::isnan(a) ? a : bias;
-    }
-  }
 };
 
 // Largest |v| of a self-attention: v = Wv h + bv with h = LN(x) (1 + scale) +

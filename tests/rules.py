@@ -15,16 +15,11 @@ SHIM = r"""
 using namespace xc;
 extern "C" {
 float score_bound(const float* gq, const float* gk, int D, int rope) { return qk_score_bound(gq, gk, D, rope != 0); }
-double self_bound(const float* w_ada, const float* b_ada, const float* wv, const float* bv, int C, int Dc, double cond_max) {
-  RowBound m, v;
-  m.add(w_ada, b_ada, (size_t)2 * C, Dc);
-  v.add(wv, bv, C, C);
-  return self_value_bound(m, v, C, Dc, cond_max);
+double self_bound(double mod_norm, double mod_bias, double v_norm, double v_bias, int C, int Dc, double cond_max) {
+  return self_value_bound({mod_norm, mod_bias}, {v_norm, v_bias}, C, Dc, cond_max);
 }
-double cross_bound(const float* wv, const float* bv, int C, double cond_max) {
-  RowBound v;
-  v.add(wv, bv, C, C);
-  return cross_value_bound(v, C, cond_max);
+double cross_bound(double v_norm, double v_bias, int C, double cond_max) {
+  return cross_value_bound({v_norm, v_bias}, C, cond_max);
 }
 int wave_rows(long long rows, int chunks) { return adaln_wave_rows(rows, chunks); }
 int f32_waves(long long Lk) { return attention_f32_waves(Lk); }
@@ -50,8 +45,8 @@ def lib():
     out = ctypes.CDLL(so)
     f, d, i, ll = ctypes.c_float, ctypes.c_double, ctypes.c_int, ctypes.c_longlong
     p = np.ctypeslib.ndpointer(np.float32, flags="C_CONTIGUOUS")
-    for name, res, args in (("score_bound", f, [p, p, i, i]), ("self_bound", d, [p, p, p, p, i, i, d]),
-                            ("cross_bound", d, [p, p, i, d]), ("bounded", i, [f, d, ll]), ("wave_rows", i, [ll, i]),
+    for name, res, args in (("score_bound", f, [p, p, i, i]), ("self_bound", d, [d, d, d, d, i, i, d]),
+                            ("cross_bound", d, [d, d, i, d]), ("bounded", i, [f, d, ll]), ("wave_rows", i, [ll, i]),
                             ("f32_waves", i, [ll]), ("tile", i, [i, i, i, i, i]), ("splits", i, [ll, ll, ll, ll]),
                             ("f32_tile", i, [i, i, i, i]), ("wide_waves", i, [i, ll, i, ll, i])):
         getattr(out, name).restype, getattr(out, name).argtypes = res, args

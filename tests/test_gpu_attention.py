@@ -196,3 +196,13 @@ def test_value_range(sign, head_dim, cross, monkeypatch):
     sc = _Scores(monkeypatch)
     _run(w, blob)
     assert 40 < (sc.hi if sign > 0 else -sc.lo) < 64
+
+
+@pytest.mark.parametrize("row", [0, 255])
+def test_value_range_of_one_row(row):
+    """Values of 2^105 in one column only, the first and the last."""
+    w, blob, t, _, _ = _lean_workload(128, False, 1.9, 1)
+    t["wv"][row] *= 2.0 ** 105
+    t["bv"][row] *= 2.0 ** 105
+    t["wo"][:, row] *= 2.0 ** -105
+    _run(w, blob)

@@ -93,14 +93,17 @@ def test_value_bounds_hold(action):
     x = next(iter(synth.latent_stream(m, synth.StreamParams(1, 0.9, 0.02), 0, 1))).astype(np.float64)
     x[0] = 1e4 * np.eye(256)[3]  # a LayerNorm output of sqrt(C) in one column
     _, (_, v) = orc.block(0, x, orc.cond(500.0, a), None)
-    c = np.ascontiguousarray
-    bound = rules.lib().self_bound(c(w["w_ada"]), c(w["b_ada"]), c(w["wv"]), c(w["bv"]), 256, m.cond_dim, max(1.0, action))
+
+    def rows(weight, bias):
+        return np.linalg.norm(weight.astype(np.float64), axis=1).max(), np.abs(bias).max()
+
+    mod = rows(w["w_ada"][:2 * 256], w["b_ada"][:2 * 256])
+    bound = rules.lib().self_bound(*mod, *rows(w["wv"], w["bv"]), 256, m.cond_dim, max(1.0, action))
     assert np.abs(v).max() <= bound <= 200 * np.abs(v).max()
-    bound = rules.lib().cross_bound(c(w["wv_c"]), c(w["bv_c"]), 256, float(np.abs(cond).max()))
+    bound = rules.lib().cross_bound(*rows(w["wv_c"], w["bv_c"]), 256, float(np.abs(cond).max()))
     assert np.abs(orc.cross_kv[0][1]).max() <= bound <= 200 * np.abs(orc.cross_kv[0][1]).max()
     w["wv"][5, 7] = math.nan
-    assert not rules.lib().bounded(16.6, rules.lib().self_bound(c(w["w_ada"]), c(w["b_ada"]), c(w["wv"]), c(w["bv"]), 256,
-                                                               m.cond_dim, 1.0), 64)
+    assert not rules.lib().bounded(16.6, rules.lib().self_bound(*mod, *rows(w["wv"], w["bv"]), 256, m.cond_dim, 1.0), 64)
 
 
 def test_adaln_wave_rows():
