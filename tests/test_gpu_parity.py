@@ -210,14 +210,12 @@ def test_bf16_wide_skip_path(width, gate):
         ls.close()
 
 
-# Hidden sizes that are no multiple of 256 put the QKV projection (and the
-# cross-attention q and condition key / value projections) on the
-# two-workgroup GEMM and its QKV epilogue, whose tile height (64 * MT rows)
-# the library picks from the tile count on 256 CUs: N = 3C = 1152 at L = 300
-# takes MT = 1 (its per-lane sums of squares padded from 16 to 32 for the
-# reduce-scatter); N = 1920 (C = 640, 5 heads of 128) takes MT = 3 at L = 5000
-# (48 padded to 64) and MT = 4 at L = 7000, where the output and MLP-down
-# products take MT = 2; hidden 2048 at L = 7020 puts those two on MT = 4.
+# The QKV epilogue of the small tiles (which hidden sizes that are no multiple
+# of 256 always take, in the cross-attention q and condition key / value
+# projections too) at each tile height, which sets how the per-lane sums of squares
+# are padded for the reduce-scatter.  On 256 CUs: 64 x 128 tiles at L = 300 (16
+# sums padded to 32), 192 x 128 at C = 640, L = 5000 (48 padded to 64) and 128 x 128
+# at L = 7000; hidden 2048 at L = 7020 puts every product on 256 x 256.
 BF_TWO_WG = {
     "h384-d64-L300-rope-cross": synth.with_model(synth.Workload(
         "bf16-2wg-3blk-h384-d64-L300",
@@ -235,7 +233,7 @@ BF_TWO_WG = {
         "bf16-2wg-1blk-h640-d128-L7000",
         synth.ModelShape(1, 640, 5, 128, 1280, 256, 16, synth.BF16, 2, 2, (synth.ViewGroup(2, 1, 50, 70),)),
         synth.GateParams(), synth.StreamParams(2, 0.999, 0.02)), rope=1),
-    # the output and MLP-down products (N = 2048, no multiple of 192) on 256-row tiles
+    # the output and MLP-down products on 256-row tiles
     "h2048-d128-L7020-oproj-down-mt4": synth.Workload(
         "bf16-2wg-1blk-h2048-d128-L7020",
         synth.ModelShape(1, 2048, 16, 128, 2048, 256, 16, synth.BF16, 1, 2, (synth.ViewGroup(2, 1, 54, 65),)),
@@ -245,9 +243,9 @@ BF_TWO_WG = {
 
 @pytest.mark.parametrize("name", list(BF_TWO_WG))
 def test_bf16_two_workgroup_qkv_epilogue(name):
-    """The two-workgroup kernel's QKV epilogue (per-head RMSNorm, rotation, q /
-    K / V^T cache stores) at every tile height, head_dim 64 and 128, against
-    the oracle: pass outputs, residuals, r_hat and the key / value caches."""
+    """The QKV epilogue (per-head RMSNorm, rotation, q / K / V^T cache stores) at
+    every height of the small tiles, head_dim 64 and 128, against the oracle:
+    pass outputs, residuals, r_hat and the key / value caches."""
     w = BF_TWO_WG[name]
     ls = _ls(w, compute=np.float32)
     try:
