@@ -426,9 +426,11 @@ __global__ __launch_bounds__(64 * kWaves, 1) void attn_bf16_kernel(const bf16* _
 // interleaved runs): running maximum, 32-query waves 829 us; the same without
 // the maximum 852; this kernel with both exponentials before one MFMA and dot
 // products 783, one exponential per MFMA 769 (739 on another box), adds
-// instead of dot products 727 there.  Counters: the matrix units are busy 65%
-// of the cycles and the clock falls from 1.95 to 1.75 GHz as the cycles do:
-// what remains is the chip's power limit.
+// instead of dot products 727 there.  Counters: the matrix units are busy 64%
+// of the cycles at 1.83 GHz; a loop of nothing but MFMAs holds 1.77 GHz.  So the
+// clock is near what the chip's power allows, and 36% of the cycles are idle
+// for the matrix units: the instructions between the MFMAs, and each tile's wait
+// for all of its DMA.  How they share these cycles was not measured.
 //
 // The MFMAs are asm statements because the compiler otherwise keeps S in
 // AGPRs and copies it out for the exponentials.  It does not see them as
@@ -1005,7 +1007,8 @@ size_t attention_workspace_floats(int L, int Lk, int H, int D) {
 
 // bounded: no running maximum (the limits and their reasons:
 // attention_bounded); otherwise the running-maximum kernel keeps p <= 2^8
-// whatever the scores.  Its time at the shape above is 823 us.
+// whatever the scores.  At the shape above, in turn on one card: 810 us against 751
+// bounded (24 heads of 64: 1017 and 825).
 //
 // bf16 requirements (checked by the caller): D in {64, 128}; Q has Mpad >=
 // roundup(L, 256) rows per head; the caches have Lcap >= roundup(Lk, 64) rows,
