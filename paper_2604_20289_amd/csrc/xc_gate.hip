@@ -73,6 +73,7 @@ constexpr int kCamUnroll = 8;                         // row loads in flight per
 constexpr int kDecThreads = 1024;                   // threads of the decision workgroup
 constexpr int kDecPairs = kDecThreads / kRec;       // (workgroup, group) records it reads at a time
 constexpr int kDecLoads = 6;                        // records per thread in flight
+constexpr int kDecMany = 16;                        // ... while there are that many
 
 // The decision.  evaluate == 0: the block is computed without a test (warmup,
 // forced pass, step-0 force, first visit): clear the flag and the staleness.
@@ -81,7 +82,9 @@ constexpr int kDecLoads = 6;                        // records per thread in fli
 // and keeps one field of one group; the threads of a (group, field) are then
 // summed in thread order through LDS.  (256 threads that read whole records
 // and reduced all 8 fields by shuffles, one group after another: 8.5 us at 672
-// records, 12.9 us at 3 groups of 448.)
+// records, 12.9 us at 3 groups of 448.)  Many groups or rows take 16 records per
+// thread at a time, not 6: 5 groups of about 8400 104 -> 90 us, 8 groups of 7200 131
+// -> 116.
 __device__ void decide(const double* records, int n_wg, const GateArgs& ga, const GateState& gs, int sb, int b,
                        int evaluate) {
   const int tid = threadIdx.x;
@@ -111,12 +114,24 @@ __device__ void decide(const double* records, int n_wg, const GateArgs& ga, cons
   const int f = tid % kRec, p0 = tid / kRec, pairs = n_wg * G;
   double v = 0.0;
   if (p0 < stride) {
-    for (int q = p0; q < pairs; q += stride * kDecLoads) {
+    auto record = [&](int p) __attribute__((always_inline)) {
+      const int w = p / G, g = p - w * G;
+      return records + ((long long)w * kMaxGroups + g) * kRec + f;
+    };
+    int q = p0;
+    for (; q + stride * (kDecMany - 1) < pairs; q += stride * kDecMany) {  // many groups or rows
+      double d[kDecMany];
+#pragma unroll
+      for (int u = 0; u < kDecMany; ++u) d[u] = *record(q + u * stride);
+#pragma unroll
+      for (int u = 0; u < kDecMany; ++u) v = f == 3 ? fmax(v, d[u]) : v + d[u];
+    }
+    for (; q < pairs; q += stride * kDecLoads) {
       double d[kDecLoads];
 #pragma unroll
       for (int u = 0; u < kDecLoads; ++u) {
-        const int p = q + u * stride, w = p / G, g = p - w * G;
-        d[u] = p < pairs ? records[((long long)w * kMaxGroups + g) * kRec + f] : 0.0;  // 0 changes neither sum nor max
+        const int p = q + u * stride;
+        d[u] = p < pairs ? *record(p) : 0.0;  // 0 changes neither sum nor max
       }
 #pragma unroll
       for (int u = 0; u < kDecLoads; ++u) v = f == 3 ? fmax(v, d[u]) : v + d[u];
